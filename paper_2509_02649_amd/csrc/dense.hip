@@ -18,9 +18,8 @@
 // multiple of 64, padded with the identity (factor) or zeros (FP64 Gram), so the
 // blocked kernels never see a ragged edge.  One FP64 Gram H64 (with any dense,
 // lambda-independent penalty folded in) serves all lambdas; each lambda has its
-// own FP32 matrix, overwritten by its Cholesky factor (FP32 diagonal blocks, the
-// blocks below them as FP16 pairs in the same 32-bit slots), and the inverses of
-// its 64 x 64 diagonal blocks.
+// own FP32 matrix, overwritten by its Cholesky factor below the diagonal blocks (as FP16
+// pairs in the same 32-bit slots), and the inverses of its 64 x 64 diagonal blocks.
 #include "fk_internal.h"
 
 #include <cmath>
@@ -590,12 +589,6 @@ __device__ inline double recip64(double x) {
   e = fma(-x, r, 1.0);
   return fma(r, e, r);
 }
-__device__ inline double recip_t(double x) { return recip64(x); }
-// 1/x for a positive normal FP32 x: hardware reciprocal and one Newton step (about 1 ulp).
-__device__ inline float recip_t(float x) {
-  const float r = __builtin_amdgcn_rcpf(x);
-  return fmaf(r, fmaf(-x, r, 1.0f), r);
-}
 
 // The same update for the two block columns kb and kb + 1 at once, over the panels
 // k < kb:  A[i][kb] -= sum L[i][k] L[kb][k]^T  and (i > kb) A[i][kb+1] -= sum
@@ -718,42 +711,40 @@ __global__ __launch_bounds__(256) void k_left_update2_sum(float* __restrict__ A,
   *dst = d;
 }
 
-// Factor the diagonal block kb of every lambda (one workgroup per lambda) in Real (FP32, or FP64
-// when the launch shape asks for it); write L_kk (lower) back and inv(L_kk) to Linv[l][kb].
+// The diagonal block kb of every lambda (one workgroup per lambda) factored in FP64, for launch
+// shapes that ask for it (diag64): inv(L_kk) to Linv[l][kb]; L_kk itself is read by nothing.
 // Within the 64 x 64 block the sweep is right-looking:
 // Thread (r, q) = (tid / 8, tid % 8) keeps entries r, q + 8u (u = 0..7) of the block, and
 // of T below, in registers.  Unscaled: at step j column j has received every
 // update, its owners publish it to P[.][j] (never written again), one barrier, and each row
-// below applies a[r][k] -= f P[k][j] with f = P[r][j] / P[j][j].  Then L[r][c] = P[r][c] /
-// sqrt(P[c][c]).  The same row operations turn the identity into T = diag(sqrt P) inv(L):
+// below applies a[r][k] -= f P[k][j] with f = P[r][j] / P[j][j].  The same row operations turn the identity into T = diag(sqrt P) inv(L):
 // T[i][c] = delta_ic - sum_{k<i} (P[i][k] / P[k][k]) T[k][c], so row j of T is final at step j,
 // is published with column j (two-slot LDS buffer), and rows r > j take t[r][.] -= f T[j][.]
 // in the same step: one sweep of 64 barriers for the factor and its inverse.
 constexpr int kPotrfThreads = 512;
-template <typename Real>
-__global__ __launch_bounds__(kPotrfThreads) void k_potrf_diag(float* __restrict__ A, int Np, int kb,
+__global__ __launch_bounds__(kPotrfThreads) void k_potrf_diag64(const float* __restrict__ A, int Np, int kb,
                                                     float* __restrict__ Linv, int* flags) {
-  __shared__ Real P[NB][NB + 1];
-  __shared__ Real trow[2][NB];
-  __shared__ Real piv[NB], sq[NB], rsq[NB];
+  __shared__ double P[NB][NB + 1];
+  __shared__ double trow[2][NB];
+  __shared__ double piv[NB], rsq[NB];
   __shared__ int bad;
   constexpr int TPR = kPotrfThreads / NB, EPT = NB / TPR;   // threads per row, entries per thread
   const int l = blockIdx.x;
-  float* Ab = A + (size_t)l * Np * Np + (size_t)kb * NB * Np + kb * NB;
+  const float* Ab = A + (size_t)l * Np * Np + (size_t)kb * NB * Np + kb * NB;
   const int r = threadIdx.x / TPR, q = threadIdx.x % TPR;
-  Real a[EPT], t[EPT];
+  double a[EPT], t[EPT];
 #pragma unroll
   for (int u = 0; u < EPT; ++u) {
     const int k = TPR * u + q;
-    a[u] = (k <= r) ? (Real)Ab[(size_t)r * Np + k] : Real(0);
-    t[u] = (k == r) ? Real(1) : Real(0);
+    a[u] = (k <= r) ? (double)Ab[(size_t)r * Np + k] : double(0);
+    t[u] = (k == r) ? double(1) : double(0);
   }
   if (threadIdx.x == 0) bad = 0;
   // unrolled, so that the register holding column j is known at compile time
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     if (q == (j % TPR) && r >= j) {
-      Real v = a[0];
+      double v = a[0];
 #pragma unroll
       for (int u = 1; u < EPT; ++u)
         if (u == (j / TPR)) v = a[u];
@@ -766,26 +757,26 @@ __global__ __launch_bounds__(kPotrfThreads) void k_potrf_diag(float* __restrict_
     __syncthreads();
     // all loads first and unconditionally (rows k < j of P[.][j] are not yet written:
     // their values are discarded by the select), so the reads share one wait
-    const Real pj = P[j][j];
-    const Real prj = P[r][j];
-    Real pk[EPT], tv[EPT];
+    const double pj = P[j][j];
+    const double prj = P[r][j];
+    double pk[EPT], tv[EPT];
 #pragma unroll
     for (int u = 0; u < EPT; ++u) {
       pk[u] = P[TPR * u + q][j];
       tv[u] = trow[j & 1][TPR * u + q];
     }
-    const bool badj = !(pj > Real(0));  // non-positive or NaN pivot
-    const Real rp = recip_t(badj ? Real(1) : pj);
-    const Real f = r > j ? prj * rp : Real(0);
+    const bool badj = !(pj > double(0));  // non-positive or NaN pivot
+    const double rp = recip64(badj ? double(1) : pj);
+    const double f = r > j ? prj * rp : double(0);
 #pragma unroll
     for (int u = 0; u < EPT; ++u) {
       const int k = TPR * u + q;
-      const Real upd = fma(-f, pk[u], a[u]);
+      const double upd = fma(-f, pk[u], a[u]);
       a[u] = (k > j && k <= r) ? upd : a[u];
       t[u] = fma(-f, tv[u], t[u]);   // T[j][c] = 0 for c > j: no change there
     }
     if (threadIdx.x == 0) {
-      piv[j] = badj ? Real(1) : pj;
+      piv[j] = badj ? double(1) : pj;
       if (badj) bad = 1;
     }
   }
@@ -794,29 +785,234 @@ __global__ __launch_bounds__(kPotrfThreads) void k_potrf_diag(float* __restrict_
   for (int u = 0; u < EPT; ++u) a[u] = t[u];
   __syncthreads();   // the last pivot (thread 0, after the last step's barrier)
   if (threadIdx.x < NB) {
-    const Real d = sqrt(piv[threadIdx.x]);
-    sq[threadIdx.x] = d;
-    rsq[threadIdx.x] = Real(1) / d;
+    rsq[threadIdx.x] = 1.0 / sqrt(piv[threadIdx.x]);
   }
   __syncthreads();
   float* Li = Linv + ((size_t)l * (Np / NB) + kb) * NB * NB;
-  const Real rs = rsq[r];
+  const double rs = rsq[r];
 #pragma unroll
   for (int u = 0; u < EPT; ++u) {
     const int c = TPR * u + q;
     Li[r * NB + c] = (c <= r) ? (float)(a[u] * rs) : 0.0f;
   }
-#pragma unroll
-  for (int u = 0; u < NB * NB / kPotrfThreads; ++u) {
-    const int i = threadIdx.x + kPotrfThreads * u, rr = i / NB, c = i - rr * NB;
-    float v = 0.0f;
-    if (c == rr) v = (float)sq[c];
-    else if (c < rr) v = (float)(P[rr][c] * rsq[c]);
-    Ab[(size_t)rr * Np + c] = v;
-  }
   if (threadIdx.x == 0 && bad) {
     atomicOr(&flags[kFlagNotPD], 1);
     atomicMin(&flags[kFlagNotPD + 1], l);
+  }
+}
+
+// The diagonal block kb of every lambda factored in FP32, and (PANEL) the panel below it.
+//
+// The 128 x 64 matrix [A_kk; I] in LDS is eliminated by columns: the top half becomes L_kk and the
+// bottom half W = inv(L_kk)^T (a row of either half takes the same column operations).  Four panels of
+// 16 columns.  In a panel a lane holds one row's 16 entries; lanes 0-15 are the panel's diagonal rows
+// (in both working waves), lanes 16-47 the four other 16-row blocks that are not zero (3 - b of A,
+// b + 1 of W, at panel b).  Column j: the pivot and the multipliers are broadcast from the diagonal
+// rows with v_readlane, so the 64 dependent column steps meet no LDS round trip and no barrier.
+// Between panels the four 16 x 16 blocks of the next panel's columns are updated on the matrix cores,
+// one per wave; the later columns' blocks by waves 2 and 3 during the next panel.
+// Bound by the chain of column steps (about 105 cycles each, 1700 per panel measured; a broadcast by
+// DPP with one wave for all rows took 2400).  The kernel this replaced published every column through
+// LDS with a barrier per step: 19.2 us per block against 7.7 alone, 8.6 with the panel and 9.9 with
+// the panel and its update (N = 4225).  Factorization at N = 4225: 2.25 -> 1.08 ms at one lambda, 12.3
+// -> 11.2 ms at 64.  L_kk is not stored: the updates read finished panels only, the solves inv(L_kk).
+//
+// PANEL: the workgroups of a lambda (one per block row i >= kb) all factor the diagonal block
+// themselves and then finish their own panel tile L[i][kb] = A[i][kb] W, which saves the launch of
+// k_trsm_panel; row i = kb writes Linv.  UPD (with PANEL): the block column first takes its remaining
+// term, A[i][kb] -= L[i][kb-1] L[kb][kb-1]^T (the diagonal tile in every workgroup), which saves the
+// launch of k_left_update.  Wave w holds rows 16 w .. of the 64 x 64 tiles, as four 16 x 16
+// accumulator blocks.
+constexpr int LDP = NB + 4;   // row stride of the elimination's LDS matrix
+template <bool PANEL, bool UPD>
+__global__ __launch_bounds__(256) void k_factor_diag(float* __restrict__ A, int Np, int kb,
+                                                     float* __restrict__ Linv, int nlam, int* flags) {
+  __shared__ __align__(16) float S[2 * NB * LDP];
+  static_assert(sizeof(S) >= 2 * sizeof(SplitTile), "the split tiles share the elimination's memory");
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  int l = blockIdx.x, i = 0;
+  if constexpr (PANEL) xcd_place(Np / NB - kb, nlam, &l, &i);
+  const int ib = kb + i;
+  float* Al = A + (size_t)l * Np * Np;
+  float* mine = Al + (size_t)ib * NB * Np + kb * NB;
+  // the diagonal tile and this workgroup's own tile in accumulator layout: block cb, element v is
+  // row 16 w + 4 lk + v, column 16 cb + li (blocks above the diagonal of the diagonal tile unused)
+  floatx4 dg[4], own[4];
+  {
+    const float* src = Al + (size_t)kb * NB * Np + kb * NB;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const size_t o = (size_t)(16 * w + 4 * lk + v) * Np + 16 * cb + li;
+        dg[cb][v] = src[o];
+        if (PANEL) own[cb][v] = mine[o];
+      }
+  }
+  if constexpr (UPD) {
+    SplitTile& Ts = *reinterpret_cast<SplitTile*>(S);
+    SplitTile& Ds = *(reinterpret_cast<SplitTile*>(S) + 1);
+    const uint32_t* gi = reinterpret_cast<const uint32_t*>(Al + (size_t)ib * NB * Np + (kb - 1) * NB);
+    const uint32_t* gd = reinterpret_cast<const uint32_t*>(Al + (size_t)kb * NB * Np + (kb - 1) * NB);
+    uint4 ra[4], rb[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int idx = tid + q * 256, r = idx / (NB / 4), c = (idx % (NB / 4)) * 4;
+      ra[q] = *reinterpret_cast<const uint4*>(gi + (size_t)r * Np + c);
+      rb[q] = *reinterpret_cast<const uint4*>(gd + (size_t)r * Np + c);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int idx = tid + q * 256, r = idx / (NB / 4), c = (idx % (NB / 4)) * 4;
+      split_stage(Ts, split_off(r, c), ra[q]);
+      split_stage(Ds, split_off(r, c), rb[q]);
+    }
+    __syncthreads();
+    floatx4 ad[4] = {}, adx[4] = {}, ao[4] = {}, aox[4] = {};
+#pragma unroll
+    for (int k = 0; k < NB; k += 32) {
+      const int oa = split_off(16 * w + li, k + 8 * lk);
+      const half8 th = *reinterpret_cast<const half8*>(&Ts.hi[oa]), tl = *reinterpret_cast<const half8*>(&Ts.lo[oa]);
+      const half8 dh = *reinterpret_cast<const half8*>(&Ds.hi[oa]), dl = *reinterpret_cast<const half8*>(&Ds.lo[oa]);
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) {
+        const int o = split_off(16 * cb + li, k + 8 * lk);
+        const half8 bh = *reinterpret_cast<const half8*>(&Ds.hi[o]), bl = *reinterpret_cast<const half8*>(&Ds.lo[o]);
+        ad[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dh, bh, ad[cb], 0, 0, 0);
+        ao[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(th, bh, ao[cb], 0, 0, 0);
+        adx[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dh, bl, adx[cb], 0, 0, 0);
+        aox[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(th, bl, aox[cb], 0, 0, 0);
+        adx[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dl, bh, adx[cb], 0, 0, 0);
+        aox[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(tl, bh, aox[cb], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        dg[cb][v] -= fmaf(adx[cb][v], 1.f / kSplitScale, ad[cb][v]);
+        own[cb][v] -= fmaf(aox[cb][v], 1.f / kSplitScale, ao[cb][v]);
+      }
+    __syncthreads();   // the split tiles are read: their memory becomes the elimination's
+  }
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * w + 4 * lk + v, c = 16 * cb + li;
+      S[r * LDP + c] = dg[cb][v];
+      S[(NB + r) * LDP + c] = r == c ? 1.f : 0.f;
+    }
+  __syncthreads();
+  // Block t of column block c takes its term of panel b: rows c.. of A (t < 4 - c), then rows 0 .. b
+  // of W.  Lane group lk supplies k = 4 lk + e of both operands at product e.
+  auto trail = [&](int b, int c, int t) {
+    const int r0 = t < 4 - c ? 16 * (c + t) : NB + 16 * (t - (4 - c));
+    const float4 av = *reinterpret_cast<const float4*>(S + (r0 + li) * LDP + 16 * b + 4 * lk);
+    const float4 bv = *reinterpret_cast<const float4*>(S + (16 * c + li) * LDP + 16 * b + 4 * lk);
+    float* cp = S + (r0 + 4 * lk) * LDP + 16 * c + li;
+    floatx4 acc = {cp[0], cp[LDP], cp[2 * LDP], cp[3 * LDP]};
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.x, bv.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.y, bv.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.z, bv.z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.w, bv.w, acc, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) cp[v * LDP] = acc[v];
+  };
+  bool bad = false;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    if (w < 2) {
+      // lane's row: group 0 the diagonal rows, groups 1 and 2 the wave's two other blocks; group 3
+      // repeats the diagonal rows and is not stored
+      const int o = 2 * w + lk - 1;
+      const int row = (lk == 0 || lk == 3) ? 16 * b + li
+                                           : (o < 3 - b ? 16 * (b + 1 + o) + li : NB + 16 * (o - (3 - b)) + li);
+      float* rp = S + row * LDP + 16 * b;
+      float a[16];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 v = *reinterpret_cast<const float4*>(rp + 4 * q);
+        a[4 * q] = v.x;
+        a[4 * q + 1] = v.y;
+        a[4 * q + 2] = v.z;
+        a[4 * q + 3] = v.w;
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const float p = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[j]), j));
+        bad = bad || !(p > 0.f);   // non-positive or NaN pivot: reported, the values are not used
+        // a[j] / sqrt(p): hardware 1 / sqrt (1 ulp) and one Newton step, applied to the product so
+        // that it and the correction are computed side by side
+        const float rs = __builtin_amdgcn_rsqf(p), l0 = a[j] * rs;
+        a[j] = fmaf(l0, fmaf(-0.5f * p * rs, rs, 0.5f), l0);
+#pragma unroll
+        for (int k = j + 1; k < 16; ++k)
+          a[k] = fmaf(-a[j], __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[j]), k)), a[k]);
+      }
+      if (lk == 1 || lk == 2 || (lk == 0 && w == 0)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<float4*>(rp + 4 * q) = make_float4(a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]);
+      }
+    }
+    if (w >= 2 && b >= 1) {
+      int cnt = 0;
+#pragma unroll
+      for (int c = b + 1; c < 4; ++c)
+#pragma unroll
+        for (int t = 0; t < 4 - c + b; ++t)
+          if ((cnt++ & 1) == w - 2) trail(b - 1, c, t);
+    }
+    __syncthreads();
+    if (b < 3) {
+      trail(b, b + 1, w);   // the next panel's column block: four blocks, one per wave
+      __syncthreads();
+    }
+  }
+  const float* W = S + NB * LDP;
+  if (!PANEL || i == 0) {
+    float* Li = Linv + ((size_t)l * (Np / NB) + kb) * NB * NB;
+#pragma unroll
+    for (int u = 0; u < NB * NB / 256; ++u) {
+      const int e = tid + 256 * u, r = e / NB, c = e % NB;
+      Li[e] = c <= r ? W[c * LDP + r] : 0.f;
+    }
+    if (tid == 0 && bad) {
+      atomicOr(&flags[kFlagNotPD], 1);
+      atomicMin(&flags[kFlagNotPD + 1], l);
+    }
+    return;
+  }
+  if constexpr (PANEL) {
+    // own tile into the top half (rows 16 w .. of it are written and read by wave w only), times W,
+    // whose blocks below the diagonal are zero
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) S[(16 * w + 4 * lk + v) * LDP + 16 * cb + li] = own[cb][v];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    floatx4 acc[4] = {};
+#pragma unroll
+    for (int kq = 0; kq < 4; ++kq) {
+      const float4 av = *reinterpret_cast<const float4*>(S + (16 * w + li) * LDP + 16 * kq + 4 * lk);
+      const float* wr = W + (16 * kq + 4 * lk) * LDP + li;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int cb = kq; cb < 4; ++cb)
+          acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(e == 0 ? av.x : e == 1 ? av.y : e == 2 ? av.z : av.w,
+                                                         wr[e * LDP + 16 * cb], acc[cb], 0, 0, 0);
+    }
+    uint32_t* dst = reinterpret_cast<uint32_t*>(mine);
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        dst[(size_t)(16 * w + 4 * lk + v) * Np + 16 * cb + li] = split_pack(acc[cb][v]);
   }
 }
 
@@ -1569,19 +1765,42 @@ static int update_split(int wgs, int kb, int part_tiles) {
   return std::max(ns, 1);
 }
 
+// Most workgroups of a block column (rows x lambdas) whose panel is solved in the launch that factors
+// the diagonal block, every workgroup factoring it for itself: up to four such workgroups fit a CU, so
+// 1024 run at once and the launch costs one factorization, against two launches.  Whole factorization,
+// fused up to 0 / 512 / 1024 / 8192 workgroups: N = 4225, one lambda 1401 / 1076 / 1078 / 1078 us; 8
+// lambdas 2463 / 2198 / 2181 / 2182; N = 1089, 64 lambdas 601 / 573 / 561 / 569.  A block column that
+// also takes the term of the panel before it is fused at any size: two launches saved and the panel
+// tile read once (64 lambdas, N = 4225: 11.40 ms up to 1024 workgroups, 11.20 always).
+constexpr int kFusedPanelWgs = 1024;
+
 // Factor A32[l] = L L^T for every lambda: left-looking blocked Cholesky, per block column an
 // update with the finished panels (one pass over the column), the factorization of the
 // diagonal block, the solve of the panel below it.
 static fk_status factor_all(fk_ctx* ctx, const SolveLayout& s, const DenseShape& sh) {
   const int nb = s.Np / NB;
-  auto finish = [&](int kb) {   // diagonal block and the panel below it
+  // diagonal block and the panel below it; upd: block column kb first takes its term of panel kb - 1
+  auto finish = [&](int kb, bool upd) {
+    const int rem = nb - kb - 1;
+    const bool fused = !sh.diag64 && (upd || (rem + 1) * s.nlam <= kFusedPanelWgs);
+    if (upd && !fused)
+      hipLaunchKernelGGL(k_left_update, dim3((nb - kb) * s.nlam), dim3(256), 0, ctx->stream, s.A32, s.Np, kb, kb - 1,
+                         kb, s.nlam);
+    if (fused) {
+      if (upd)
+        hipLaunchKernelGGL((k_factor_diag<true, true>), dim3((rem + 1) * s.nlam), dim3(256), 0, ctx->stream, s.A32,
+                           s.Np, kb, s.Linv, s.nlam, ctx->flags);
+      else
+        hipLaunchKernelGGL((k_factor_diag<true, false>), dim3((rem + 1) * s.nlam), dim3(256), 0, ctx->stream, s.A32,
+                           s.Np, kb, s.Linv, s.nlam, ctx->flags);
+      return;
+    }
     if (sh.diag64)
-      hipLaunchKernelGGL(k_potrf_diag<double>, dim3(s.nlam), dim3(kPotrfThreads), 0, ctx->stream, s.A32, s.Np, kb, s.Linv,
+      hipLaunchKernelGGL(k_potrf_diag64, dim3(s.nlam), dim3(kPotrfThreads), 0, ctx->stream, s.A32, s.Np, kb, s.Linv,
                          ctx->flags);
     else
-      hipLaunchKernelGGL(k_potrf_diag<float>, dim3(s.nlam), dim3(kPotrfThreads), 0, ctx->stream, s.A32, s.Np, kb, s.Linv,
-                         ctx->flags);
-    const int rem = nb - kb - 1;
+      hipLaunchKernelGGL((k_factor_diag<false, false>), dim3(s.nlam), dim3(256), 0, ctx->stream, s.A32, s.Np, kb,
+                         s.Linv, s.nlam, ctx->flags);
     if (rem > 0)
       hipLaunchKernelGGL(k_trsm_panel, dim3(rem * s.nlam), dim3(256), 0, ctx->stream, s.A32, s.Np, kb, s.Linv,
                          s.nlam);
@@ -1601,16 +1820,15 @@ static fk_status factor_all(fk_ctx* ctx, const SolveLayout& s, const DenseShape&
         hipLaunchKernelGGL(k_left_update2<false>, dim3(wgs), dim3(256), 0, ctx->stream, s.A32, s.Np, kb, s.nlam, 1,
                            nullptr);
       }
-      finish(kb);
-      hipLaunchKernelGGL(k_left_update, dim3((nb - kb - 1) * s.nlam), dim3(256), 0, ctx->stream, s.A32, s.Np,
-                         kb + 1, kb, kb + 1, s.nlam);
-      finish(kb + 1);
+      finish(kb, false);
+      finish(kb + 1, true);
       kb += 2;
     } else {
-      if (kb > 0)
+      const bool one = kb == 1;   // a single panel before it: its term goes with the diagonal block
+      if (kb > 1)
         hipLaunchKernelGGL(k_left_update, dim3((nb - kb) * s.nlam), dim3(256), 0, ctx->stream, s.A32, s.Np, kb, 0,
                            kb, s.nlam);
-      finish(kb);
+      finish(kb, one);
       kb += 1;
     }
   }
