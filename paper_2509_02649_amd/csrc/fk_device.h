@@ -10,21 +10,17 @@ namespace fk {
 // for NaN or |x| outside [-2 pi, 2 pi).
 __device__ __forceinline__ bool to_fixed(double x, double scale, uint32_t nf_fix, uint32_t* U,
                                          int* flags) {
-  if (!(x == x) || isinf(x)) {
-    atomicOr(&flags[kFlagNaN], 1);
-    return false;
-  }
   const double two_pi = 6.283185307179586476925;
-  if (x < -two_pi || x >= two_pi) {
-    atomicOr(&flags[kFlagRange], 1);
+  if (!(x >= -two_pi && x < two_pi)) {   // NaN or Inf, else out of range
+    atomicOr(&flags[(x - x == 0.0) ? kFlagRange : kFlagNaN], 1);
     return false;
   }
   if (x < -3.14159265358979323846) x += two_pi;
   if (x >= 3.14159265358979323846) x -= two_pi;
-  double u = (x + 3.14159265358979323846) * scale;   // in [0, nf * 2^fb]
-  uint64_t v = (uint64_t)__double2ll_rn(u);
+  const double u = (x + 3.14159265358979323846) * scale;   // in [0, nf * 2^fb], nf * 2^fb = 2^31
+  uint32_t v = __double2uint_rn(u);
   if (v >= nf_fix) v -= nf_fix;                       // x == pi - tiny rounding up to nf
-  *U = (uint32_t)v;
+  *U = v;
   return true;
 }
 

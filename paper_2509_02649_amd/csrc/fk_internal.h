@@ -173,11 +173,10 @@ struct DenseShape {
 // words the second pass writes, instead of the weights, each point's position in
 // the row-grouped records of the first pass (b.wts1), one word per point.
 struct Sort2Bufs {
+  uint32_t* rowtot = nullptr;   // points per bin row (zeroed by the caller, see sort2)
   uint32_t* cnt1 = nullptr;
-  uint32_t* off1 = nullptr;
   uint64_t* start1 = nullptr;
   uint32_t* cnt2 = nullptr;
-  uint32_t* off2 = nullptr;
   uint32_t* crd1 = nullptr;
   uint32_t* wts1 = nullptr;
 };
@@ -186,9 +185,11 @@ int sort2_words(int nw);
 // Buffers for any shape with at most kSortBlkMax first-pass workgroups and slices of at least
 // kSortSliceMin points.
 void sort2_carve(Carve& cv, int64_t n, int nbx, int wv, Sort2Bufs* b);
+// totals: sort2_totals(nbx) words that the caller has set to zero.
+size_t sort2_totals(int nbx);
 fk_status sort2(hipStream_t st, const void* X, fk_dtype dt, int64_t n, int64_t xstride, const void* Y, int nw,
-                int nf, int fb, int W, double scale, int tshift, int nbx, const T1Shape& shape, const Sort2Bufs& b,
-                uint32_t* crd, uint32_t* wts, uint64_t* start, int* flags);
+                int nf, int fb, int W, double scale, int tshift, int nbx, const T1Shape& shape, Sort2Bufs b,
+                uint32_t* totals, uint32_t* crd, uint32_t* wts, uint64_t* start, int* flags);
 
 }  // namespace fk
 

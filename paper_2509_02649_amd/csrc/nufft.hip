@@ -783,15 +783,19 @@ size_t type1_workspace(int d, int64_t n, int nw, int K, double eps) {
       cv.take<uint32_t>((size_t)n * (3 + nw));        // records
       return cv.off;
     }
-    cv.take<double>((size_t)C * nf * nf);          // FP64 grid
-    cv.take<double>((size_t)C * nf * L * 2);        // row-FFT output
     BinGeom g = bin_geom(nf, C, n, kind);
     if (kind == Spread2::kRows) {                   // bin starts for the finest bins any shape takes
       const BinGeom g2 = bin_geom(nf, C, n, kind, 2);
       if (g2.nb > g.nb) g = g2;
     }
-    cv.take<uint32_t>((size_t)g.nb * g.nblk);
-    cv.take<uint32_t>((size_t)g.nb);
+    cv.take<double>((size_t)C * nf * nf);          // FP64 grid
+    if (kind != Spread2::kAtomic) {
+      cv.take<uint32_t>(sort2_totals(g.nbx));
+    } else {
+      cv.take<uint32_t>((size_t)g.nb * g.nblk);
+      cv.take<uint32_t>((size_t)g.nb);
+    }
+    cv.take<double>((size_t)C * nf * L * 2);        // row-FFT output
     cv.take<uint64_t>((size_t)g.nb + 1);
     if (kind != Spread2::kAtomic) {
       const int wv = sort2_words(nw);
@@ -1055,8 +1059,6 @@ fk_status type1(fk_ctx* ctx, int d, int64_t n, fk_dtype dt, const void* X, int64
     return FK_OK;
   }
   if (d != 2) return FK_EINVAL;
-  double* grid = cv.take<double>((size_t)C * nf * nf);
-  double* rowfft = cv.take<double>((size_t)C * nf * L * 2);
   const Spread2 kind = spread2_kind(nw, nf, W, n);
   const bool split = kind != Spread2::kAtomic;   // two-pass sort, then an MFMA spread
   const int wv = sort2_words(nw);
@@ -1065,8 +1067,11 @@ fk_status type1(fk_ctx* ctx, int d, int64_t n, fk_dtype dt, const void* X, int64
     const BinGeom g2 = bin_geom(nf, C, n, kind, 2);
     if (g2.nb > gmax.nb) gmax = g2;
   }
-  uint32_t* cnt = cv.take<uint32_t>((size_t)gmax.nb * gmax.nblk);
-  uint32_t* totals = cv.take<uint32_t>((size_t)gmax.nb);
+  // the sort's totals follow the grid, so that one fill clears both
+  double* grid = cv.take<double>((size_t)C * nf * nf);
+  uint32_t* cnt = split ? nullptr : cv.take<uint32_t>((size_t)gmax.nb * gmax.nblk);
+  uint32_t* totals = cv.take<uint32_t>(split ? sort2_totals(gmax.nbx) : (size_t)gmax.nb);
+  double* rowfft = cv.take<double>((size_t)C * nf * L * 2);
   uint64_t* start = cv.take<uint64_t>((size_t)gmax.nb + 1);
   uint32_t* rec = cv.take<uint32_t>((size_t)n * (split ? 2 : 2 + nw));
   // second sorted array: weight words (outer-product spread) or, for the channel-row
@@ -1080,11 +1085,13 @@ fk_status type1(fk_ctx* ctx, int d, int64_t n, fk_dtype dt, const void* X, int64
     const BinGeom g = bin_geom(nf, C, n, kind, sh.mb);
     if (info) info->bin = g.T;
     FK_HIP(hipEventRecord(ev[0], ctx->stream));
-    FK_HIP(hipMemsetAsync(grid, 0, sizeof(double) * C * nf * nf, ctx->stream));
+    size_t clear = sizeof(double) * C * nf * nf;
+    if (split) clear = (size_t)(reinterpret_cast<char*>(totals + sort2_totals(g.nbx)) - reinterpret_cast<char*>(grid));
+    FK_HIP(hipMemsetAsync(grid, 0, clear, ctx->stream));
     if (split) {
       // records for the MFMA spreads: two-pass sort, coordinates and weight words
-      fk_status s2 = sort2(ctx->stream, X, dt, n, xstride, Y, nw, nf, fb, W, scale, g.tshift, g.nbx, sh, sb, rec, wts,
-                           start, ctx->flags);
+      fk_status s2 = sort2(ctx->stream, X, dt, n, xstride, Y, nw, nf, fb, W, scale, g.tshift, g.nbx, sh, sb, totals,
+                           rec, wts, start, ctx->flags);
       if (s2 != FK_OK) return s2;
     } else {
       hipLaunchKernelGGL(k_bin_count, dim3(g.nblk), dim3(256), sizeof(uint32_t) * g.nb, ctx->stream, X, dt, n,

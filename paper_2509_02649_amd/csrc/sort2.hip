@@ -33,7 +33,7 @@ constexpr int BT = 1024;       // points per staged batch, one per thread
 constexpr int KMAX = 256;      // largest bucket count (nf / MB for nf <= 1024)
 
 struct Stage {
-  unsigned long long cur[KMAX];   // next output position of every bucket
+  uint32_t cur[KMAX];             // next output position of every bucket
   uint32_t hist[KMAX];            // bucket counts of the current batch
   uint32_t lofs[KMAX];            // their exclusive prefix sums
   uint32_t total;
@@ -82,7 +82,7 @@ __device__ __forceinline__ void write_coords(St& sm, uint2* __restrict__ crd_out
   const int tid = threadIdx.x;
   if ((uint32_t)tid < sm.total) {
     const int b = sm.sbin[tid];
-    crd_out[sm.cur[b] + (tid - sm.lofs[b])] = sm.scrd[tid];
+    crd_out[(size_t)sm.cur[b] + (tid - sm.lofs[b])] = sm.scrd[tid];
   }
 }
 
@@ -120,20 +120,20 @@ __device__ __forceinline__ void stage_batch(Stage& sm, int nk, bool ok, int key,
   for (uint32_t q = tid; q < total * 4; q += BT) {
     const uint32_t s = q >> 2;
     const int b = sm.sbin[s];
-    wts_out[(sm.cur[b] + (s - sm.lofs[b])) * 4 + (q & 3)] = sm.swts[q];
+    wts_out[((size_t)sm.cur[b] + (s - sm.lofs[b])) * 4 + (q & 3)] = sm.swts[q];
   }
   advance_cursors(sm, nk);
 }
 
 // Pass 1 counts: bucket = bin row of every valid point, one row of nbx counts per
-// workgroup (contiguous chunks of the input).  Each thread takes CU1 points per
-// step, their loads issued together.
+// workgroup (contiguous chunks of the input), and the totals rowtot (zeroed beforehand).  Each thread
+// takes CU1 points per step, their loads issued together.
 constexpr int CU1 = 4;
 template <typename TX>
 __global__ __launch_bounds__(BT) void k_s2_count1(const TX* __restrict__ X, int64_t n, int64_t xstride,
                                                   double scale, uint32_t nf_fix, int fb, uint32_t wbias,
                                                   int tshift, int nbx, int64_t chunk, uint32_t* __restrict__ cnt,
-                                                  int* flags) {
+                                                  uint32_t* __restrict__ rowtot, int* flags) {
   __shared__ uint32_t hist[KMAX];
   for (int i = threadIdx.x; i < nbx; i += blockDim.x) hist[i] = 0;
   __syncthreads();
@@ -157,11 +157,112 @@ __global__ __launch_bounds__(BT) void k_s2_count1(const TX* __restrict__ X, int6
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < nbx; i += blockDim.x) cnt[(int64_t)blockIdx.x * nbx + i] = hist[i];
+  for (int i = threadIdx.x; i < nbx; i += blockDim.x) {
+    cnt[(int64_t)blockIdx.x * nbx + i] = hist[i];
+    if (hist[i]) atomicAdd(&rowtot[i], hist[i]);
+  }
 }
 
-// Pass 1 scatter.  off holds, per workgroup and bucket, the count of the bucket's
-// points in earlier workgroups; start1 the bucket starts.  The inputs of the next
+// Exclusive prefix sums over the 1024 threads of a workgroup (sh: 16 words); the sum in total.
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* sh, uint32_t* total) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  uint32_t x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) sh[w] = x;
+  __syncthreads();
+  uint32_t before = 0, all = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const uint32_t y = sh[i];
+    before += i < w ? y : 0u;
+    all += y;
+  }
+  __syncthreads();   // sh may be reused
+  *total = all;
+  return before + x - v;
+}
+
+// Sum of a[0 .. count) by a workgroup, its loads coalesced and independent.
+__device__ __forceinline__ uint32_t block_sum(const uint32_t* __restrict__ a, int64_t count, uint32_t* sh) {
+  uint32_t s = 0, total;
+#pragma unroll 4
+  for (int64_t i = threadIdx.x; i < count; i += 1024) s += a[i];
+  (void)block_scan(s, sh, &total);
+  return total;
+}
+
+// Offsets of pass 1 (in place of its counts cnt[k][b]): cnt[k][b] becomes the position at which
+// workgroup k's points of bucket b start, in the order of the workgroups (the order of the input).
+// rowtot: the buckets' totals.  Workgroup b takes bucket b: a thread per first-pass workgroup (at most
+// kSortBlkMax = 1024), all columns side by side (one workgroup walking them took 17 us for 152 x 64
+// counts and 57 for 512 x 256, this takes 4).
+__global__ __launch_bounds__(1024) void k_s2_scan1(uint32_t* __restrict__ cnt, int nk, int nblk,
+                                                   const uint32_t* __restrict__ rowtot,
+                                                   uint64_t* __restrict__ start1) {
+  __shared__ uint32_t sh[16];
+  const int b = blockIdx.x, k = threadIdx.x;
+  const uint32_t v = k < nblk ? cnt[(int64_t)k * nk + b] : 0u;
+  const uint32_t base = block_sum(rowtot, b, sh);
+  uint32_t total;
+  const uint32_t p = base + block_scan(v, sh, &total);
+  if (k < nblk) cnt[(int64_t)k * nk + b] = p;
+  if (k == 0) {
+    start1[b] = base;
+    if (b == nk - 1) start1[nk] = (uint64_t)base + total;
+  }
+}
+
+// Workgroup `blk` of the second pass: its row and its part [q0, q1) of the row's points.  A row of len
+// points has ceil(len / slice_pts) slices of equal size, so the work is even for any density; the grid
+// holds one workgroup per row more than n / slice_pts.  False past the last slice.
+__device__ __forceinline__ bool slice_of(const uint64_t* __restrict__ start1, int nbx, uint32_t slice_pts,
+                                         uint32_t blk, int* row, uint64_t* q0, uint64_t* q1) {
+  __shared__ uint32_t found[4];
+  static_assert(KMAX % 64 == 0, "rows per lane");
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    constexpr int RP = KMAX / 64;   // rows per lane
+    uint32_t ns[RP], sum = 0;
+#pragma unroll
+    for (int i = 0; i < RP; ++i) {
+      const int r = lane * RP + i;
+      const uint32_t len = r < nbx ? (uint32_t)(start1[r + 1] - start1[r]) : 0u;
+      ns[i] = len / slice_pts + (len % slice_pts != 0);
+      sum += ns[i];
+    }
+    uint32_t x = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    if (lane == 63) found[3] = x;
+    uint32_t first = x - sum;
+#pragma unroll
+    for (int i = 0; i < RP; ++i) {
+      if (blk >= first && blk < first + ns[i]) {
+        found[0] = lane * RP + i;
+        found[1] = blk - first;
+        found[2] = ns[i];
+      }
+      first += ns[i];
+    }
+  }
+  __syncthreads();
+  if (blk >= found[3]) return false;
+  *row = (int)found[0];
+  const uint64_t p0 = start1[*row], len = start1[*row + 1] - p0;
+  *q0 = p0 + len * found[1] / found[2];
+  *q1 = p0 + len * (found[1] + 1) / found[2];
+  return true;
+}
+
+// Pass 1 scatter.  off holds, per workgroup and bucket, where its points of the bucket
+// start.  The inputs of the next
 // batch are loaded (unconditionally, index clamped to the chunk) while the current
 // batch is ranked, staged and written.
 template <typename TX>
@@ -170,14 +271,13 @@ __global__ __launch_bounds__(BT) void k_s2_scatter1(const TX* __restrict__ X, in
                                                     double scale, uint32_t nf_fix, int fb, uint32_t wbias,
                                                     int tshift, int nbx, int64_t chunk,
                                                     const uint32_t* __restrict__ off,
-                                                    const uint64_t* __restrict__ start1,
                                                     uint2* __restrict__ crd1, uint4* __restrict__ wts1,
                                                     int* flags) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   Stage& sm = *reinterpret_cast<Stage*>(smem_raw);
   const int tid = threadIdx.x;
   for (int b = tid; b < nbx; b += BT) {
-    sm.cur[b] = start1[b] + off[(int64_t)blockIdx.x * nbx + b];
+    sm.cur[b] = off[(int64_t)blockIdx.x * nbx + b];
     sm.hist[b] = 0;
   }
   __syncthreads();
@@ -223,18 +323,17 @@ __global__ __launch_bounds__(BT) void k_s2_scatter1(const TX* __restrict__ X, in
   }
 }
 
-// Pass 2 counts: workgroup (bx, slice) counts the bin columns of its slice of row bx,
-// CU1 loads in flight per thread.
+// Pass 2 counts: a workgroup counts the bin columns of its slice of a row, cnt2[workgroup][by]; CU1 loads
+// in flight per thread.
 __global__ __launch_bounds__(BT) void k_s2_count2(const uint2* __restrict__ crd1,
-                                                  const uint64_t* __restrict__ start1, int slices, int fb,
+                                                  const uint64_t* __restrict__ start1, uint32_t slice_pts, int fb,
                                                   uint32_t wbias, int nf, int tshift, int nbx,
                                                   uint32_t* __restrict__ cnt2) {
   __shared__ uint32_t hist[KMAX];
-  for (int i = threadIdx.x; i < nbx; i += blockDim.x) hist[i] = 0;
-  __syncthreads();
-  const int bx = blockIdx.x / slices, sl = blockIdx.x - bx * slices;
-  const uint64_t p0 = start1[bx], len = start1[bx + 1] - p0;
-  const uint64_t q0 = p0 + len * sl / slices, q1 = p0 + len * (sl + 1) / slices;
+  for (int i = threadIdx.x; i < nbx; i += BT) hist[i] = 0;
+  int bx;
+  uint64_t q0, q1;
+  if (!slice_of(start1, nbx, slice_pts, blockIdx.x, &bx, &q0, &q1)) return;
   for (uint64_t p = q0 + threadIdx.x; p < q1; p += (uint64_t)CU1 * BT) {
     uint32_t y[CU1];
 #pragma unroll
@@ -244,39 +343,63 @@ __global__ __launch_bounds__(BT) void k_s2_count2(const uint2* __restrict__ crd1
       if (p + (uint64_t)u * BT < q1) atomicAdd(&hist[window_bin(y[u], fb, wbias, nf, tshift)], 1u);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < nbx; i += blockDim.x) cnt2[(int64_t)blockIdx.x * nbx + i] = hist[i];
+  for (int i = threadIdx.x; i < nbx; i += BT) cnt2[(int64_t)blockIdx.x * nbx + i] = hist[i];
 }
 
-// Pass 2 offsets, one workgroup per row bx: off2[(bx, slice, by)] = count of bin
-// (bx, by) in earlier slices of the row, and start[bx * nbx + by] = the bin start.
-__global__ __launch_bounds__(KMAX) void k_s2_scan2(const uint32_t* __restrict__ cnt2,
-                                                  const uint64_t* __restrict__ start1, int slices, int nbx,
-                                                  uint32_t* __restrict__ off2, uint64_t* __restrict__ start) {
-  __shared__ uint64_t tot[KMAX];
-  const int bx = blockIdx.x, by = threadIdx.x;
-  uint64_t run = 0;
-  if (by < nbx) {
-    for (int s = 0; s < slices; ++s) {
-      const int64_t i = ((int64_t)bx * slices + s) * nbx + by;
-      off2[i] = (uint32_t)run;
-      run += cnt2[i];
+// Offsets of pass 2 (in place of its counts), one workgroup per row: cnt2[slice][by] becomes the position
+// at which the slice's points of bin (row, by) start, in the order of the slices, and start[row nbx + by]
+// the bin's start.  A row's slices are consecutive workgroups of the second pass; thread (g, by) takes
+// the g-th part of them.
+__global__ __launch_bounds__(1024) void k_s2_scan2(uint32_t* __restrict__ cnt2, const uint64_t* __restrict__ start1,
+                                                   uint32_t slice_pts, int nbx, uint64_t* __restrict__ start) {
+  __shared__ uint32_t sh[16];
+  __shared__ uint32_t part[1024], tot[KMAX];
+  const int row = blockIdx.x, t = threadIdx.x;
+  auto slices = [&](int r) -> uint32_t {
+    const uint32_t len = (uint32_t)(start1[r + 1] - start1[r]);
+    return len / slice_pts + (len % slice_pts != 0);
+  };
+  uint32_t first;   // slices of the rows before
+  (void)block_scan(t < row ? slices(t) : 0u, sh, &first);
+  const uint32_t ns = slices(row);
+  const int groups = 1024 / nbx, by = t % nbx, g = t / nbx;   // threads past groups nbx idle
+  const bool on = g < groups;
+  const uint32_t s0 = (uint32_t)((uint64_t)ns * g / groups), s1 = (uint32_t)((uint64_t)ns * (g + 1) / groups);
+  uint32_t* c = cnt2 + (int64_t)first * nbx + by;
+  uint32_t sum = 0;
+  if (on) {
+#pragma unroll 4
+    for (uint32_t s = s0; s < s1; ++s) sum += c[(int64_t)s * nbx];
+  }
+  part[t] = sum;
+  __syncthreads();
+  uint32_t before = 0, all = 0;   // the bin's points in earlier groups, and in all
+  if (on)
+    for (int i = 0; i < groups; ++i) {
+      const uint32_t v = part[i * nbx + by];
+      before += i < g ? v : 0u;
+      all += v;
     }
-    tot[by] = run;
+  if (t < nbx) tot[by] = all;
+  uint32_t total;
+  const uint32_t pre = block_scan(t < nbx ? all : 0u, sh, &total);
+  const uint32_t base = (uint32_t)start1[row];
+  if (t < nbx) {
+    start[(int64_t)row * nbx + t] = base + pre;
+    tot[t] = base + pre;
+    if (t == 0 && row == nbx - 1) start[(int64_t)nbx * nbx] = (uint64_t)base + total;
   }
   __syncthreads();
-  if (by == 0) {
-    uint64_t acc = start1[bx];
-    for (int i = 0; i < nbx; ++i) {
-      const uint64_t t = tot[i];
-      tot[i] = acc;
-      acc += t;
+  if (on) {
+    uint32_t run = tot[by] + before;
+#pragma unroll 4
+    for (uint32_t s = s0; s < s1; ++s) {
+      const uint32_t v = c[(int64_t)s * nbx];
+      c[(int64_t)s * nbx] = run;
+      run += v;
     }
   }
-  __syncthreads();
-  if (by < nbx) start[(int64_t)bx * nbx + by] = tot[by];
-  if (bx == nbx - 1 && by == 0) start[(int64_t)nbx * nbx] = start1[nbx];
 }
-
 
 // ---------------------------------------------------------------- narrow records
 // The same two passes for 0..7 weight channels (the outer-product spread): records of
@@ -290,7 +413,7 @@ constexpr int kPosPpt = 8;   // points per thread of the position pass (116 KB o
 template <int WV, int P = narrow_ppt<WV>()>
 struct StageN {
   static constexpr int NPT = P;
-  unsigned long long cur[KMAX];
+  uint32_t cur[KMAX];
   uint32_t hist[KMAX];
   uint32_t lofs[KMAX];
   uint32_t total;
@@ -336,13 +459,13 @@ __device__ __forceinline__ void write_batch_n(StageN<WV, P>& sm, uint2* __restri
   const uint32_t total = sm.total;
   for (uint32_t q = threadIdx.x; q < total; q += BT) {
     const int b = sm.sbin[q];
-    crd_out[sm.cur[b] + (q - sm.lofs[b])] = sm.scrd[q];
+    crd_out[(size_t)sm.cur[b] + (q - sm.lofs[b])] = sm.scrd[q];
   }
   if constexpr (WV > 0) {
     for (uint32_t q = threadIdx.x; q < total * WV; q += BT) {
       const uint32_t s = q / WV;
       const int b = sm.sbin[s];
-      wts_out[(sm.cur[b] + (s - sm.lofs[b])) * WV + q % WV] = sm.swts[q];
+      wts_out[((size_t)sm.cur[b] + (s - sm.lofs[b])) * WV + q % WV] = sm.swts[q];
     }
   }
 }
@@ -352,7 +475,6 @@ __global__ __launch_bounds__(BT) void k_s2n_scatter1(const TX* __restrict__ X, i
                                                      const TX* __restrict__ Y, int nw, double scale,
                                                      uint32_t nf_fix, int fb, uint32_t wbias, int tshift, int nbx,
                                                      int64_t chunk, const uint32_t* __restrict__ off,
-                                                     const uint64_t* __restrict__ start1,
                                                      uint2* __restrict__ crd1, uint32_t* __restrict__ wts1,
                                                      int* flags) {
   constexpr int NPT = narrow_ppt<WV>();
@@ -360,7 +482,7 @@ __global__ __launch_bounds__(BT) void k_s2n_scatter1(const TX* __restrict__ X, i
   StageN<WV>& sm = *reinterpret_cast<StageN<WV>*>(smem_raw);
   const int tid = threadIdx.x;
   for (int b = tid; b < nbx; b += BT) {
-    sm.cur[b] = start1[b] + off[(int64_t)blockIdx.x * nbx + b];
+    sm.cur[b] = off[(int64_t)blockIdx.x * nbx + b];
     sm.hist[b] = 0;
   }
   __syncthreads();
@@ -442,22 +564,21 @@ __global__ __launch_bounds__(BT) void k_s2n_scatter2(const uint2* __restrict__ c
                                                      const uint32_t* __restrict__ wts1,
                                                      const uint64_t* __restrict__ start1,
                                                      const uint32_t* __restrict__ off2,
-                                                     const uint64_t* __restrict__ start, int slices, int fb,
+                                                     uint32_t slice_pts, int fb,
                                                      uint32_t wbias, int nf, int tshift, int nbx,
                                                      uint2* __restrict__ crd, uint32_t* __restrict__ wts) {
   constexpr int WD = WV > 0 ? WV : 1;   // divisor for the word index (no words when WV = 0)
   extern __shared__ __align__(16) unsigned char smem_raw[];
   StageN<WV, NPT>& sm = *reinterpret_cast<StageN<WV, NPT>*>(smem_raw);
   const int tid = threadIdx.x;
-  const int bx = blockIdx.x / slices, sl = blockIdx.x - bx * slices;
+  int bx;
+  uint64_t q0, q1;
+  if (!slice_of(start1, nbx, slice_pts, blockIdx.x, &bx, &q0, &q1)) return;
   for (int b = tid; b < nbx; b += BT) {
-    sm.cur[b] = start[(int64_t)bx * nbx + b] + off2[(int64_t)blockIdx.x * nbx + b];
+    sm.cur[b] = off2[(int64_t)blockIdx.x * nbx + b];
     sm.hist[b] = 0;
   }
   __syncthreads();
-  const uint64_t p0 = start1[bx], len = start1[bx + 1] - p0;
-  const uint64_t q0 = p0 + len * sl / slices, q1 = p0 + len * (sl + 1) / slices;
-  if (q0 >= q1) return;
   const int lane = tid & 63;
   const uint64_t wb = (uint64_t)(tid & ~63);
   uint2 nU[NPT];
@@ -514,96 +635,90 @@ __global__ __launch_bounds__(BT) void k_s2n_scatter2(const uint2* __restrict__ c
 #undef FK_FETCH2N
 }
 
-// Offsets of pass 1: off[k][b] = number of points of bucket b in workgroups < k,
-// and start1[b] (start1[nk] = number of valid points).  One workgroup of 1024
-// threads: thread (grp, b) sums a range of workgroups, the group sums are
-// scanned, then each range is rewritten as running offsets.
-constexpr int SG = 1024 / KMAX;   // workgroup ranges per bucket
-__global__ __launch_bounds__(1024) void k_s2_scan1(const uint32_t* __restrict__ cnt, int nk, int nblk,
-                                                  uint32_t* __restrict__ off, uint64_t* __restrict__ start1) {
-  __shared__ uint64_t part[SG][KMAX];
-  __shared__ uint64_t tot[KMAX];
-  const int b = threadIdx.x % KMAX, grp = threadIdx.x / KMAX;
-  const int per = (nblk + SG - 1) / SG;
-  const int k0 = grp * per, k1 = min(nblk, k0 + per);
-  uint64_t s = 0;
-  if (b < nk)
-    for (int k = k0; k < k1; ++k) s += cnt[(int64_t)k * nk + b];
-  part[grp][b] = s;
-  __syncthreads();
-  if (grp == 0 && b < nk) {
-    uint64_t run = 0;
-    for (int g = 0; g < SG; ++g) {
-      const uint64_t t = part[g][b];
-      part[g][b] = run;
-      run += t;
-    }
-    tot[b] = run;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t acc = 0;
-    for (int i = 0; i < nk; ++i) {
-      start1[i] = acc;
-      acc += tot[i];
-    }
-    start1[nk] = acc;
-  }
-  if (b < nk) {
-    uint64_t run = part[grp][b];
-    for (int k = k0; k < k1; ++k) {
-      off[(int64_t)k * nk + b] = (uint32_t)run;
-      run += cnt[(int64_t)k * nk + b];
-    }
-  }
-}
-
 struct Sort2Geom {
-  int nblk1, slices;
-  int64_t chunk1;
+  int nblk1;            // workgroups of the first pass
+  int64_t chunk1;       // their points
+  uint32_t slice_pts;   // points per workgroup of the second pass (at most)
+  int nblk2;            // its workgroups: every row's last slice may be short
 };
 
-// First pass: up to blk workgroups of at least 65536 points each; second pass: slices of about
-// slice_pts points per bin row (at most 256).
+// First pass: up to blk workgroups of at least 8192 points (two staged batches of narrow records; a
+// workgroup of 65536, the earlier minimum, left 1e7 points to 152 of the 256 CUs and 30011 to one: 97 and
+// 98 us for the scatter against 61 and 27).  Second pass: slices of slice_pts points, smaller ones
+// where n would not give 512 of them.
 Sort2Geom sort2_geom(int64_t n, int nbx, int blk, int64_t slice_pts) {
   Sort2Geom g;
-  g.nblk1 = (int)std::min<int64_t>(blk, std::max<int64_t>(1, (n + 65535) / 65536));
+  g.nblk1 = (int)std::min<int64_t>(blk, std::max<int64_t>(1, (n + 8191) / 8192));
   g.chunk1 = (n + g.nblk1 - 1) / g.nblk1;
-  g.slices = (int)std::min<int64_t>(256, std::max<int64_t>(1, (n / nbx + slice_pts - 1) / slice_pts));
+  g.slice_pts = (uint32_t)std::max<int64_t>(4096, std::min<int64_t>(slice_pts, n / 512));
+  g.nblk2 = (int)(nbx + n / g.slice_pts);
   return g;
 }
 
-// Counts (shared with the wide records), scans, and the narrow-record scatters.
-template <int WV>
-fk_status sort2_narrow(hipStream_t st, const void* X, fk_dtype dt, int64_t n, int64_t xstride, const void* Y, int nw,
-                       uint32_t nf_fix, int fb, uint32_t wbias, double scale, int tshift, int nbx,
-                       const Sort2Geom& g, const Sort2Bufs& b, uint32_t* crd, uint32_t* wts, uint64_t* start,
-                       int* flags) {
-  const size_t lds = sizeof(StageN<WV>);
-  const int nf = (int)(nf_fix >> fb);
-  if (dt == FK_F64) {
-    const double* Xd = static_cast<const double*>(X);
-    hipLaunchKernelGGL(k_s2_count1<double>, dim3(g.nblk1), dim3(BT), 0, st, Xd, n, xstride, scale, nf_fix, fb,
-                       wbias, tshift, nbx, g.chunk1, b.cnt1, flags);
-    hipLaunchKernelGGL(k_s2_scan1, dim3(1), dim3(1024), 0, st, b.cnt1, nbx, g.nblk1, b.off1, b.start1);
-    hipLaunchKernelGGL((k_s2n_scatter1<double, WV>), dim3(g.nblk1), dim3(BT), lds, st, Xd, n, xstride,
-                       static_cast<const double*>(Y), nw, scale, nf_fix, fb, wbias, tshift, nbx, g.chunk1, b.off1,
-                       b.start1, reinterpret_cast<uint2*>(b.crd1), b.wts1, flags);
-  } else {
-    const float* Xf = static_cast<const float*>(X);
-    hipLaunchKernelGGL(k_s2_count1<float>, dim3(g.nblk1), dim3(BT), 0, st, Xf, n, xstride, scale, nf_fix, fb,
-                       wbias, tshift, nbx, g.chunk1, b.cnt1, flags);
-    hipLaunchKernelGGL(k_s2_scan1, dim3(1), dim3(1024), 0, st, b.cnt1, nbx, g.nblk1, b.off1, b.start1);
-    hipLaunchKernelGGL((k_s2n_scatter1<float, WV>), dim3(g.nblk1), dim3(BT), lds, st, Xf, n, xstride,
-                       static_cast<const float*>(Y), nw, scale, nf_fix, fb, wbias, tshift, nbx, g.chunk1, b.off1,
-                       b.start1, reinterpret_cast<uint2*>(b.crd1), b.wts1, flags);
+struct SortArgs {
+  hipStream_t st;
+  int64_t n, xstride;
+  int nw, nf, fb, tshift, nbx;
+  uint32_t nf_fix, wbias;
+  double scale;
+  uint64_t* start;
+  int* flags;
+};
+
+// Counts and offsets of the first pass.
+template <typename TX>
+void sort2_first(const SortArgs& a, const TX* X, const Sort2Geom& g, const Sort2Bufs& b) {
+  hipLaunchKernelGGL(k_s2_count1<TX>, dim3(g.nblk1), dim3(BT), 0, a.st, X, a.n, a.xstride, a.scale, a.nf_fix, a.fb,
+                     a.wbias, a.tshift, a.nbx, g.chunk1, b.cnt1, b.rowtot, a.flags);
+  hipLaunchKernelGGL(k_s2_scan1, dim3(a.nbx), dim3(1024), 0, a.st, b.cnt1, a.nbx, g.nblk1, b.rowtot, b.start1);
+}
+
+// Counts, offsets and scatter of the second pass.
+template <int WV, bool kPosition, int NPT>
+void sort2_second(const SortArgs& a, const Sort2Geom& g, const Sort2Bufs& b, uint32_t* crd, uint32_t* wts) {
+  const uint2* c1 = reinterpret_cast<const uint2*>(b.crd1);
+  hipLaunchKernelGGL(k_s2_count2, dim3(g.nblk2), dim3(BT), 0, a.st, c1, b.start1, g.slice_pts, a.fb, a.wbias, a.nf,
+                     a.tshift, a.nbx, b.cnt2);
+  hipLaunchKernelGGL(k_s2_scan2, dim3(a.nbx), dim3(1024), 0, a.st, b.cnt2, b.start1, g.slice_pts, a.nbx, a.start);
+  hipLaunchKernelGGL((k_s2n_scatter2<WV, kPosition, NPT>), dim3(g.nblk2), dim3(BT), sizeof(StageN<WV, NPT>), a.st, c1,
+                     b.wts1, b.start1, b.cnt2, g.slice_pts, a.fb, a.wbias, a.nf, a.tshift, a.nbx,
+                     reinterpret_cast<uint2*>(crd), wts);
+}
+
+template <int WV, typename TX>
+void sort2_narrow(const SortArgs& a, const TX* X, const TX* Y, const Sort2Geom& g, const Sort2Bufs& b, uint32_t* crd,
+                  uint32_t* wts) {
+  sort2_first(a, X, g, b);
+  hipLaunchKernelGGL((k_s2n_scatter1<TX, WV>), dim3(g.nblk1), dim3(BT), sizeof(StageN<WV>), a.st, X, a.n, a.xstride, Y,
+                     a.nw, a.scale, a.nf_fix, a.fb, a.wbias, a.tshift, a.nbx, g.chunk1, b.cnt1,
+                     reinterpret_cast<uint2*>(b.crd1), b.wts1, a.flags);
+  sort2_second<WV, false, narrow_ppt<WV>()>(a, g, b, crd, wts);
+}
+
+// Pass 2 of the 16-word records moves the coordinates and each point's position in the pass-1 output
+// (into wts, one word per point); the weight blocks stay grouped by bin row in b.wts1.  Its records are
+// 12 B, so a batch takes kPosPpt points per thread.
+template <typename TX>
+void sort2_wide(const SortArgs& a, const TX* X, const TX* Y, const Sort2Geom& g, const Sort2Bufs& b, uint32_t* crd,
+                uint32_t* wts) {
+  sort2_first(a, X, g, b);
+  hipLaunchKernelGGL(k_s2_scatter1<TX>, dim3(g.nblk1), dim3(BT), sizeof(Stage), a.st, X, a.n, a.xstride, Y, a.nw,
+                     a.scale, a.nf_fix, a.fb, a.wbias, a.tshift, a.nbx, g.chunk1, b.cnt1,
+                     reinterpret_cast<uint2*>(b.crd1), reinterpret_cast<uint4*>(b.wts1), a.flags);
+  sort2_second<1, true, kPosPpt>(a, g, b, crd, wts);
+}
+
+template <typename TX>
+fk_status sort2_typed(const SortArgs& a, const TX* X, const TX* Y, const Sort2Geom& g, const Sort2Bufs& b,
+                      uint32_t* crd, uint32_t* wts) {
+  switch (sort2_words(a.nw)) {
+    case 0: sort2_narrow<0>(a, X, Y, g, b, crd, wts); break;
+    case 1: sort2_narrow<1>(a, X, Y, g, b, crd, wts); break;
+    case 2: sort2_narrow<2>(a, X, Y, g, b, crd, wts); break;
+    case 4: sort2_narrow<4>(a, X, Y, g, b, crd, wts); break;
+    case 8: sort2_narrow<8>(a, X, Y, g, b, crd, wts); break;
+    default: sort2_wide(a, X, Y, g, b, crd, wts); break;
   }
-  hipLaunchKernelGGL(k_s2_count2, dim3(nbx * g.slices), dim3(BT), 0, st, reinterpret_cast<const uint2*>(b.crd1),
-                     b.start1, g.slices, fb, wbias, nf, tshift, nbx, b.cnt2);
-  hipLaunchKernelGGL(k_s2_scan2, dim3(nbx), dim3(KMAX), 0, st, b.cnt2, b.start1, g.slices, nbx, b.off2, start);
-  hipLaunchKernelGGL((k_s2n_scatter2<WV, false>), dim3(nbx * g.slices), dim3(BT), lds, st,
-                     reinterpret_cast<const uint2*>(b.crd1), b.wts1, b.start1, b.off2, start, g.slices, fb, wbias,
-                     nf, tshift, nbx, reinterpret_cast<uint2*>(crd), wts);
   return hipGetLastError() == hipSuccess ? FK_OK : FK_EHIP;
 }
 
@@ -619,70 +734,33 @@ int sort2_words(int nw) {
   return wv;
 }
 
+size_t sort2_totals(int nbx) { return (size_t)nbx; }
+
 void sort2_carve(Carve& cv, int64_t n, int nbx, int wv, Sort2Bufs* b) {
-  Sort2Geom g = sort2_geom(n, nbx, kSortBlkMax, kSortSliceMin);
+  // the most first-pass workgroups and second-pass slices that any shape takes
+  const Sort2Geom g = sort2_geom(n, nbx, kSortBlkMax, kSortSliceMin);
   b->cnt1 = cv.take<uint32_t>((size_t)g.nblk1 * nbx);
-  b->off1 = cv.take<uint32_t>((size_t)g.nblk1 * nbx);
   b->start1 = cv.take<uint64_t>((size_t)nbx + 1);
-  b->cnt2 = cv.take<uint32_t>((size_t)nbx * g.slices * nbx);
-  b->off2 = cv.take<uint32_t>((size_t)nbx * g.slices * nbx);
+  b->cnt2 = cv.take<uint32_t>((size_t)g.nblk2 * nbx);
   b->crd1 = cv.take<uint32_t>((size_t)n * 2);
   b->wts1 = cv.take<uint32_t>((size_t)n * wv);
 }
 
 fk_status sort2(hipStream_t st, const void* X, fk_dtype dt, int64_t n, int64_t xstride, const void* Y, int nw,
-                int nf, int fb, int W, double scale, int tshift, int nbx, const T1Shape& shape, const Sort2Bufs& b,
-                uint32_t* crd, uint32_t* wts, uint64_t* start, int* flags) {
+                int nf, int fb, int W, double scale, int tshift, int nbx, const T1Shape& shape, Sort2Bufs b,
+                uint32_t* totals, uint32_t* crd, uint32_t* wts, uint64_t* start, int* flags) {
   if (!sort2_ok(nbx) || nw > 16 || (nf & (nf - 1)) != 0 || (nbx << tshift) != nf) return FK_EINVAL;
   if (n > (int64_t)0xffffffff) return FK_EINVAL;   // positions are 32-bit
   if (shape.sort_blk < 1 || shape.sort_blk > kSortBlkMax || shape.sort_slice < kSortSliceMin) return FK_EINVAL;
   const Sort2Geom g = sort2_geom(n, nbx, shape.sort_blk, shape.sort_slice);
-  const uint32_t nf_fix = (uint32_t)nf << fb;
+  b.rowtot = totals;
   const uint32_t one = 1u << fb;
-  const uint32_t wbias = (one - 1u) + 8u * one - ((uint32_t)W << (fb - 1));
-  const int wv = sort2_words(nw);
-  if (wv < 16) {
-    switch (wv) {
-      case 0: return sort2_narrow<0>(st, X, dt, n, xstride, Y, nw, nf_fix, fb, wbias, scale, tshift, nbx, g, b, crd,
-                                     wts, start, flags);
-      case 1: return sort2_narrow<1>(st, X, dt, n, xstride, Y, nw, nf_fix, fb, wbias, scale, tshift, nbx, g, b, crd,
-                                     wts, start, flags);
-      case 2: return sort2_narrow<2>(st, X, dt, n, xstride, Y, nw, nf_fix, fb, wbias, scale, tshift, nbx, g, b, crd,
-                                     wts, start, flags);
-      case 4: return sort2_narrow<4>(st, X, dt, n, xstride, Y, nw, nf_fix, fb, wbias, scale, tshift, nbx, g, b, crd,
-                                     wts, start, flags);
-      default: return sort2_narrow<8>(st, X, dt, n, xstride, Y, nw, nf_fix, fb, wbias, scale, tshift, nbx, g, b, crd,
-                                      wts, start, flags);
-    }
-  }
-  const size_t lds = sizeof(Stage);
-  if (dt == FK_F64) {
-    const double* Xd = static_cast<const double*>(X);
-    hipLaunchKernelGGL(k_s2_count1<double>, dim3(g.nblk1), dim3(BT), 0, st, Xd, n, xstride, scale, nf_fix, fb,
-                       wbias, tshift, nbx, g.chunk1, b.cnt1, flags);
-    hipLaunchKernelGGL(k_s2_scan1, dim3(1), dim3(1024), 0, st, b.cnt1, nbx, g.nblk1, b.off1, b.start1);
-    hipLaunchKernelGGL(k_s2_scatter1<double>, dim3(g.nblk1), dim3(BT), lds, st, Xd, n, xstride,
-                       static_cast<const double*>(Y), nw, scale, nf_fix, fb, wbias, tshift, nbx, g.chunk1, b.off1,
-                       b.start1, reinterpret_cast<uint2*>(b.crd1), reinterpret_cast<uint4*>(b.wts1), flags);
-  } else {
-    const float* Xf = static_cast<const float*>(X);
-    hipLaunchKernelGGL(k_s2_count1<float>, dim3(g.nblk1), dim3(BT), 0, st, Xf, n, xstride, scale, nf_fix, fb,
-                       wbias, tshift, nbx, g.chunk1, b.cnt1, flags);
-    hipLaunchKernelGGL(k_s2_scan1, dim3(1), dim3(1024), 0, st, b.cnt1, nbx, g.nblk1, b.off1, b.start1);
-    hipLaunchKernelGGL(k_s2_scatter1<float>, dim3(g.nblk1), dim3(BT), lds, st, Xf, n, xstride,
-                       static_cast<const float*>(Y), nw, scale, nf_fix, fb, wbias, tshift, nbx, g.chunk1, b.off1,
-                       b.start1, reinterpret_cast<uint2*>(b.crd1), reinterpret_cast<uint4*>(b.wts1), flags);
-  }
-  hipLaunchKernelGGL(k_s2_count2, dim3(nbx * g.slices), dim3(BT), 0, st, reinterpret_cast<const uint2*>(b.crd1),
-                     b.start1, g.slices, fb, wbias, nf, tshift, nbx, b.cnt2);
-  hipLaunchKernelGGL(k_s2_scan2, dim3(nbx), dim3(KMAX), 0, st, b.cnt2, b.start1, g.slices, nbx, b.off2, start);
-  // pass 2 moves the coordinates and each point's position in the pass-1 output
-  // (into wts, one word per point); the weight blocks stay grouped by bin row in b.wts1.
-  // Its records are 12 B, so a batch takes kPosPpt points per thread.
-  hipLaunchKernelGGL((k_s2n_scatter2<1, true, kPosPpt>), dim3(nbx * g.slices), dim3(BT), sizeof(StageN<1, kPosPpt>), st,
-                     reinterpret_cast<const uint2*>(b.crd1), static_cast<const uint32_t*>(nullptr), b.start1, b.off2,
-                     start, g.slices, fb, wbias, nf, tshift, nbx, reinterpret_cast<uint2*>(crd), wts);
-  return hipGetLastError() == hipSuccess ? FK_OK : FK_EHIP;
+  const SortArgs a{st,  n,      xstride, nw,
+                   nf,  fb,     tshift,  nbx,
+                   (uint32_t)nf << fb, (one - 1u) + 8u * one - ((uint32_t)W << (fb - 1)), scale, start, flags};
+  if (dt == FK_F64)
+    return sort2_typed(a, static_cast<const double*>(X), static_cast<const double*>(Y), g, b, crd, wts);
+  return sort2_typed(a, static_cast<const float*>(X), static_cast<const float*>(Y), g, b, crd, wts);
 }
 
 }  // namespace fk
