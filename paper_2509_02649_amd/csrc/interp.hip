@@ -9,6 +9,7 @@
 //   Re f(x) ~= sum_l Re(g_l) phi(l - u),  g_l = sum_q (-1)^q theta_q / Phihat(q h) e^{2 pi i q l / nf}.
 #include "fk_internal.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -298,72 +299,266 @@ __global__ __launch_bounds__(256) void k_idft_rows_pad(const double* __restrict_
   }
 }
 
-// f_t(x_j) for one coefficient set t and one chunk of points, from the padded grid in LDS.
-// Blocks: the T sets of a chunk are consecutive among the blocks one XCD receives (blocks go to
-// the 8 XCDs round robin), so the chunk's coordinates are read from HBM once per chunk and then
-// from that XCD's L2.
+// f_t(x_j) for the points of one chunk (1024 NPT points, NPT per thread) and the sets t0 .. t0 + ts - 1,
+// each set's padded grid in LDS in turn.
+//
+// Bound by LDS: w^2 reads per point and set at unrelated addresses.  All reads of a point have its base
+// address plus an offset that is the same for every lane, so lanes whose base addresses lie in different
+// banks never conflict.  The chunk is therefore ordered by the bank of the base address (a counting sort
+// over the 64 banks in LDS): lane l takes points of bank l, and the few points over a bank's share fill
+// the slots that other banks leave empty.  The kernel values are computed once per point, and kept in
+// registers for all sets.  Results are staged in LDS in the order of the input and written as runs.
+// 3e6 points x 16 sets at m = 32, w = 8: 675 us with unordered points, one set per workgroup and the
+// kernel values per set; 390 us now (LDS busy 250 of them).  Loading the next set's grid into registers
+// meanwhile costs a point per thread: 421 us.
+constexpr int kLds = 160 * 1024;
+constexpr int kBanks = 64;
 template <int W>
-__global__ __launch_bounds__(1024) void k_interp2_lds(const float* __restrict__ gpad, size_t pstride, int nf, int T,
-                                                      const void* __restrict__ Xq, fk_dtype dt, int64_t nq,
-                                                      int64_t per_chunk, int64_t nchunk, double scale, EsDev2 es,
-                                                      float* __restrict__ out, int* flags) {
-  extern __shared__ float gl[];
-  constexpr int H = W / 2;
-  const int P = nf + W;
-  const int64_t b = blockIdx.x, xcd = b & 7, k = b >> 3;
-  const int t = (int)(k % T);
-  const int64_t chunk = (k / T) * 8 + xcd;
-  if (chunk >= nchunk) return;
-  const int64_t j0 = chunk * per_chunk;
-  const int64_t j1 = min(nq, j0 + per_chunk);
-  if (j0 >= j1) return;
-  {
-    const float4* src = reinterpret_cast<const float4*>(gpad + (size_t)t * pstride);
-    float4* dst = reinterpret_cast<float4*>(gl);
-    const int n4 = (int)(pstride / 4);
-    for (int i = threadIdx.x; i < n4; i += blockDim.x) dst[i] = src[i];
-  }
+constexpr int interp_npt() { return W <= 8 ? 4 : (W <= 12 ? 2 : 1); }
+constexpr int IT = 1024;   // threads (four waves per SIMD, 128 registers each)
+
+template <int W, int NPT>
+__global__ __launch_bounds__(IT) void k_interp2_lds(const float* __restrict__ gpad, size_t pstride, int nf, int T,
+                                                      int ts, const void* __restrict__ Xq, fk_dtype dt, int64_t nq,
+                                                      double scale, EsDev2 es, int staged, float* __restrict__ out,
+                                                      int* flags) {
+  extern __shared__ __align__(16) float gl[];   // records of the ordered points, then grid and staging
+  constexpr int H = W / 2, PTS = IT * NPT, CAP = PTS / kBanks;
+  const int P = nf + W, tid = threadIdx.x;
+  const int ngrp = (T + ts - 1) / ts;
+  const int t0 = (blockIdx.x % ngrp) * ts, t1 = min(T, t0 + ts);
+  const int64_t j0 = (int64_t)(blockIdx.x / ngrp) * PTS;
+  const int count = (int)min((int64_t)PTS, nq - j0);
+  // record of a point: offsets s1, s2, base address (all ones: outside [-2 pi, 2 pi)), index in the chunk
+  struct __align__(16) Rec {
+    float s1, s2;
+    uint32_t addr, j;
+  };
+  Rec* rec = reinterpret_cast<Rec*>(gl);
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(rec + PTS);   // points, points over and slots free, per bank
+  uint32_t* over = cnt + kBanks;
+  uint32_t* hole = over + kBanks;
+  if (tid < kBanks) cnt[tid] = 0;
   __syncthreads();
   auto ld = [&](int64_t idx) -> double {
     return dt == FK_F64 ? static_cast<const double*>(Xq)[idx] : (double)static_cast<const float*>(Xq)[idx];
   };
-  // one point: f_t(x_j), or NaN and the range flag for a coordinate outside [-2 pi, 2 pi)
-  auto one = [&](int64_t j) -> float {
-    int i1, i2;
-    float s1, s2;
-    const bool ok1 = window_at(ld(j), scale, W, &i1, &s1);
-    const bool ok2 = window_at(ld(nq + j), scale, W, &i2, &s2);
-    if (!(ok1 && ok2)) {
-      atomicOr(&flags[kFlagRange], 1);
-      return __int_as_float(0x7fc00000);
-    }
-    float k1[W], k2[W];
+  constexpr uint32_t kOut = 0xffffffffu, kNone = 0xfffffffeu;   // out of range; an empty slot
+  Rec r[NPT];
+  uint32_t rank[NPT];
 #pragma unroll
-    for (int a = 0; a < W; ++a) {
-      k1[a] = es_eval2(s1 + (float)a, es);
-      k2[a] = es_eval2(s2 + (float)a, es);
+  for (int u = 0; u < NPT; ++u) {
+    const int j = u * IT + tid;
+    r[u].addr = kNone;
+    r[u].j = j;
+    if (j < count) {
+      int i1, i2;
+      const bool ok1 = window_at(ld(j0 + j), scale, W, &i1, &r[u].s1);
+      const bool ok2 = window_at(ld(nq + j0 + j), scale, W, &i2, &r[u].s2);
+      r[u].addr = ok1 && ok2 ? (uint32_t)((i1 + H) * P + (i2 + H)) : kOut;
+      if (!(ok1 && ok2)) atomicOr(&flags[kFlagRange], 1);
+      rank[u] = atomicAdd(&cnt[r[u].addr % kBanks], 1u);
     }
-    const float* gp = gl + (i1 + H) * P + (i2 + H);
-    float acc = 0.f;
-#pragma unroll
-    for (int a = 0; a < W; ++a) {
-      const float* row = gp + a * P;
-      float ra = 0.f;
-#pragma unroll
-      for (int c = 0; c < W; ++c) ra += row[c] * k2[c];
-      acc += ra * k1[a];
-    }
-    return acc;
-  };
-  // two points per thread and step (independent chains of LDS reads)
-  const int64_t stride = blockDim.x;
-  int64_t j = j0 + threadIdx.x;
-  for (; j + stride < j1; j += 2 * stride) {
-    const float a = one(j), b = one(j + stride);
-    out[(int64_t)t * nq + j] = a;
-    out[(int64_t)t * nq + j + stride] = b;
   }
-  if (j < j1) out[(int64_t)t * nq + j] = one(j);
+#pragma unroll
+  for (int u = 0; u < NPT; ++u) rec[u * IT + tid].addr = kNone;
+  __syncthreads();
+  if (tid < kBanks) {   // exclusive sums of the points over, and of the slots free, per bank
+    const int c = (int)cnt[tid];
+    uint32_t a = (uint32_t)max(0, c - CAP), b = (uint32_t)max(0, CAP - c);
+    const uint32_t a0 = a, b0 = b;
+#pragma unroll
+    for (int o = 1; o < kBanks; o <<= 1) {
+      const uint32_t x = __shfl_up(a, o, 64), y = __shfl_up(b, o, 64);
+      if (tid >= o) {
+        a += x;
+        b += y;
+      }
+    }
+    over[tid] = a - a0;
+    hole[tid] = b - b0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < NPT; ++u) {
+    if (r[u].addr == kNone) continue;
+    const uint32_t bank = r[u].addr % kBanks;
+    uint32_t slot;
+    if (rank[u] < (uint32_t)CAP) {
+      slot = rank[u] * kBanks + bank;
+    } else {
+      const uint32_t o = over[bank] + (rank[u] - CAP);   // the o-th free slot: last bank with hole[] <= o
+      int lo = 0;
+#pragma unroll
+      for (int st = kBanks / 2; st > 0; st >>= 1)
+        if (hole[lo + st] <= o) lo += st;
+      slot = (cnt[lo] + (o - hole[lo])) * kBanks + lo;
+    }
+    rec[slot] = r[u];
+  }
+  __syncthreads();
+  float k1[NPT][W], k2[NPT][W];
+  uint32_t base[NPT], jj[NPT];
+#pragma unroll
+  for (int u = 0; u < NPT; ++u) {
+    const Rec q = rec[u * IT + tid];
+    const bool real = q.addr < kNone;
+    base[u] = real ? q.addr : (uint32_t)(tid % kBanks);   // any address inside the grid, of the lane's bank
+    jj[u] = q.addr == kNone ? kNone : (q.addr == kOut ? (q.j | 0x80000000u) : q.j);
+#pragma unroll
+    for (int a = 0; a < W; ++a) {
+      k1[u][a] = es_eval2((real ? q.s1 : 0.f) + (float)a, es);
+      k2[u][a] = es_eval2((real ? q.s2 : 0.f) + (float)a, es);
+    }
+  }
+  __syncthreads();   // the records are read: the grids take their memory
+  float* so = gl + pstride;
+  const int n4 = (int)(pstride / 4);
+  for (int t = t0; t < t1; ++t) {
+    const float4* src = reinterpret_cast<const float4*>(gpad + (size_t)t * pstride);
+    for (int i = tid; i < n4; i += IT) reinterpret_cast<float4*>(gl)[i] = src[i];
+    __syncthreads();
+    float* ot = out + (int64_t)t * nq + j0;
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+      // (a branch around each point: without it the compiler issues the reads of all points at once and
+      // runs out of registers)
+      if (jj[u] == kNone) continue;
+      const float* gp = gl + base[u];
+      float acc = 0.f;
+#pragma unroll
+      for (int a = 0; a < W; ++a) {
+        const float* row = gp + a * P;
+        float ra = 0.f;
+#pragma unroll
+        for (int c = 0; c < W; ++c) ra += row[c] * k2[u][c];
+        acc += ra * k1[u][a];
+      }
+      if (jj[u] & 0x80000000u) acc = __int_as_float(0x7fc00000);
+      const uint32_t j = jj[u] & 0x7fffffffu;
+      if (staged) so[j] = acc;
+      else ot[j] = acc;
+    }
+    __syncthreads();
+    if (staged)
+      for (int j = tid; j < count; j += IT) ot[j] = so[j];
+  }
+}
+
+// ------------------------------------------------------------------ few points: direct sums
+// f_t(x_j) = Re sum_k theta_k e^{i k.x_j} in FP64, for calls so small that the grids of the type-2
+// transform cost more than the sums.  A workgroup takes DP points of one set: lane (p, s) of a wave the
+// last-axis modes s, s + 8, ... of point p, whose phases stay in registers (a rotation by e^{8 i x}
+// from one to the next), the waves the rows (the modes of the other axes) in turn.  Bound by latency at
+// the sizes that take it: 1000 points at m = 32 in 8.2 us, against 18.5 us for the three kernels of the
+// transform.
+constexpr int DP = 8;              // points per workgroup
+constexpr int DW = 8;              // waves per workgroup
+
+// sin and cos of a, |a| < 1e4: Cody-Waite reduction by pi/2 in two parts and the Taylor series on
+// [-pi/4, pi/4] (to a^17 and a^16, below 1e-16).
+__device__ __forceinline__ void sincos_small(double a, double* sn, double* cs) {
+  const double k = rint(a * 0.63661977236758134308);
+  double r = fma(-k, 1.57079632679489655800, a);
+  r = fma(-k, 6.12323399573676603587e-17, r);
+  const double z = r * r;
+  double p = 1.0 / 355687428096000.0, q = 1.0 / 20922789888000.0;
+  p = fma(p, z, -1.0 / 1307674368000.0);
+  q = fma(q, z, -1.0 / 87178291200.0);
+  p = fma(p, z, 1.0 / 6227020800.0);
+  q = fma(q, z, 1.0 / 479001600.0);
+  p = fma(p, z, -1.0 / 39916800.0);
+  q = fma(q, z, -1.0 / 3628800.0);
+  p = fma(p, z, 1.0 / 362880.0);
+  q = fma(q, z, 1.0 / 40320.0);
+  p = fma(p, z, -1.0 / 5040.0);
+  q = fma(q, z, -1.0 / 720.0);
+  p = fma(p, z, 1.0 / 120.0);
+  q = fma(q, z, 1.0 / 24.0);
+  p = fma(p, z, -1.0 / 6.0);
+  q = fma(q, z, -0.5);
+  const double s = fma(p * z, r, r), c = fma(q, z, 1.0);
+  const int n = (int)k;
+  const double u = (n & 1) ? c : s, v = (n & 1) ? s : c;
+  *sn = (n & 2) ? -u : u;
+  *cs = ((n + 1) & 2) ? -v : v;
+}
+
+__device__ __forceinline__ void rot(double& re, double& im, double cr, double ci) {
+  const double t = re * cr - im * ci;
+  im = fma(re, ci, im * cr);
+  re = t;
+}
+
+// DK: last-axis modes per lane (8 DK >= 2m + 1).
+template <int D, int DK>
+__global__ __launch_bounds__(64 * DW) void k_direct(const double2* __restrict__ theta, int m, int64_t nq, fk_dtype dt,
+                                                    const void* __restrict__ Xq, float* __restrict__ out, int* flags) {
+  __shared__ double part[DW][DP];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int p = lane & 7, s = lane >> 3;
+  const int L = 2 * m + 1;
+  const int64_t j = (int64_t)blockIdx.x * DP + p, jc = min(j, nq - 1);
+  const int t = blockIdx.y;
+  double x[D];
+  bool ok = true;
+  const double two_pi = 6.283185307179586476925;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    x[a] = dt == FK_F64 ? static_cast<const double*>(Xq)[a * nq + jc]
+                        : (double)static_cast<const float*>(Xq)[a * nq + jc];
+    ok = ok && x[a] >= -two_pi && x[a] < two_pi;
+    x[a] = ok ? x[a] : 0.0;
+  }
+  // last axis: e^{i k x} for k = -m + s + 8 q
+  double er[DK], ei[DK], br, bi;
+  sincos_small(8.0 * x[D - 1], &bi, &br);
+  sincos_small((double)(s - m) * x[D - 1], &ei[0], &er[0]);
+#pragma unroll
+  for (int q = 1; q < DK; ++q) {
+    er[q] = er[q - 1];
+    ei[q] = ei[q - 1];
+    rot(er[q], ei[q], br, bi);
+  }
+  const int rows = D == 1 ? 1 : (D == 2 ? L : L * L);
+  double acc = 0.0;
+  const double2* th = theta + (size_t)t * rows * L;
+  double cs = 1.0, sn = 0.0, dr = 1.0, di = 0.0;   // D = 2: phase of row r, and from row r to row r + DW
+  if constexpr (D == 2) {
+    sincos_small((double)(w - m) * x[0], &sn, &cs);
+    sincos_small((double)DW * x[0], &di, &dr);
+  }
+  for (int r = w; r < rows; r += DW) {
+    double sr = 0.0, si = 0.0;
+    const double2* row = th + (size_t)r * L;
+    double2 v[DK];
+#pragma unroll
+    for (int q = 0; q < DK; ++q) v[q] = row[min(s + 8 * q, L - 1)];
+#pragma unroll
+    for (int q = 0; q < DK; ++q) {
+      if (8 * q + 8 > L && s + 8 * q >= L) v[q] = make_double2(0.0, 0.0);
+      sr = fma(v[q].x, er[q], fma(-v[q].y, ei[q], sr));
+      si = fma(v[q].x, ei[q], fma(v[q].y, er[q], si));
+    }
+    if constexpr (D == 1) {
+      acc += sr;
+    } else {
+      if constexpr (D == 3) sincos_small((double)(r / L - m) * x[0] + (double)(r % L - m) * x[1], &sn, &cs);
+      acc = fma(sr, cs, fma(-si, sn, acc));
+      if constexpr (D == 2) rot(cs, sn, dr, di);
+    }
+  }
+#pragma unroll
+  for (int o = 8; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
+  if (s == 0) part[w][p] = acc;
+  __syncthreads();
+  if (threadIdx.x < DP && j < nq) {
+    double v = 0.0;
+#pragma unroll
+    for (int i = 0; i < DW; ++i) v += part[i][p];
+    if (!ok) atomicOr(&flags[kFlagRange], 1);
+    out[(int64_t)t * nq + j] = ok ? (float)v : __int_as_float(0x7fc00000);
+  }
 }
 
 static int ilog2i(int v) {
@@ -435,6 +630,64 @@ extern "C" fk_status fk_predict_workspace_size(fk_ctx* ctx, int d, int m, int nt
 
 namespace fk {
 
+template <int W, int NPT>
+static fk_status launch_interp2_n(hipStream_t st, const float* gp, size_t pst, int nf, int T, const void* Xq,
+                                  fk_dtype dt, int64_t nq, EsDev2 es, float* out, int* flags) {
+  const int64_t chunks = (nq + IT * NPT - 1) / (IT * NPT);
+  // sets per workgroup: all of them once the chunks fill the CUs twice, fewer below
+  const int ts = (int)std::max<int64_t>(1, std::min<int64_t>(T, T * chunks / 512));
+  const int64_t blocks = chunks * ((T + ts - 1) / ts);
+  if (blocks > 0x7fffffff) return FK_EINVAL;
+  const size_t grid = sizeof(float) * pst, stage = sizeof(float) * IT * NPT;
+  const size_t rec = 16 * IT * NPT + 3 * sizeof(uint32_t) * kBanks;
+  const int staged = grid + stage <= (size_t)kLds;
+  const size_t lds = std::max(rec, grid + (staged ? stage : 0));
+  hipLaunchKernelGGL((k_interp2_lds<W, NPT>), dim3((unsigned)blocks), dim3(IT), lds, st, gp, pst, nf, T, ts, Xq, dt,
+                     nq, (double)nf / (2.0 * 3.14159265358979323846), es, staged, out, flags);
+  return hipGetLastError() == hipSuccess ? FK_OK : FK_EHIP;
+}
+
+// Points per thread: as many as the registers allow, fewer where that would leave CUs without a chunk or
+// the results without room behind the grid.
+template <int W>
+static fk_status launch_interp2(hipStream_t st, const float* gp, size_t pst, int nf, int T, const void* Xq,
+                                fk_dtype dt, int64_t nq, EsDev2 es, float* out, int* flags) {
+  constexpr int NPT = interp_npt<W>();
+  auto fits = [&](int npt) {
+    return sizeof(float) * (pst + IT * npt) <= (size_t)kLds && nq * T >= (int64_t)256 * IT * npt;
+  };
+  if constexpr (NPT >= 4)
+    if (fits(4)) return launch_interp2_n<W, 4>(st, gp, pst, nf, T, Xq, dt, nq, es, out, flags);
+  if constexpr (NPT >= 2)
+    if (fits(2)) return launch_interp2_n<W, 2>(st, gp, pst, nf, T, Xq, dt, nq, es, out, flags);
+  return launch_interp2_n<W, 1>(st, gp, pst, nf, T, Xq, dt, nq, es, out, flags);
+}
+
+template <int DK>
+static void launch_direct(fk_ctx* ctx, int d, dim3 grid, const double2* th, int m, int64_t nq, fk_dtype dt,
+                          const void* Xq, float* out) {
+  if (d == 1)
+    hipLaunchKernelGGL((k_direct<1, DK>), grid, dim3(64 * DW), 0, ctx->stream, th, m, nq, dt, Xq, out, ctx->flags);
+  else if (d == 2)
+    hipLaunchKernelGGL((k_direct<2, DK>), grid, dim3(64 * DW), 0, ctx->stream, th, m, nq, dt, Xq, out, ctx->flags);
+  else
+    hipLaunchKernelGGL((k_direct<3, DK>), grid, dim3(64 * DW), 0, ctx->stream, th, m, nq, dt, Xq, out, ctx->flags);
+}
+
+// Direct sums instead of the transform, where they are estimated to take less: per point and set 0.25 ns
+// and 0.45 (d = 3: 0.65, a sine and cosine per row) ps per mode, lanes past the last mode counted
+// (measured: 0.65, 2.1 and 8.0 ns at d = 2, m = 8, 32 and 60; 4.7 and 28 ns at d = 3, m = 6 and 16; 0.23
+// at d = 1, m = 50), against what the transform costs before its first point: three launches more, and
+// grids that grow with m (about 5 us at d = 1; 9, 13 and 25 us at d = 2, m = 8, 32 and 60; 42 and 100 us
+// at d = 3, m = 6 and 16), of which three quarters are taken.
+static bool direct_ok(int d, int m, int T, int64_t nq) {
+  const int L = 2 * m + 1;
+  const double rows = std::pow((double)L, d - 1), lanes = 8.0 * (L <= 40 ? 5 : (L <= 72 ? 9 : 17));
+  const double per_point = 0.25e-3 + rows * lanes * (d == 3 ? 0.65e-6 : 0.45e-6);   // microseconds
+  const double fixed = d == 1 ? 4.0 : (d == 2 ? 6.0 + 0.2 * m : 28.0 + 1.4e-3 * rows * L);
+  return (double)nq * T * per_point <= fixed;
+}
+
 // The type-2 stage on a caller-given workspace and deconvolution table (device, plan.K + 1 doubles).
 static fk_status predict_impl(fk_ctx* ctx, const EsPlan& plan, const double* phihat, int d, int m, int T,
                               const double* theta, int64_t nq, fk_dtype dt, const void* Xq, float* out, void* ws,
@@ -442,6 +695,15 @@ static fk_status predict_impl(fk_ctx* ctx, const EsPlan& plan, const double* phi
   fk_status st = reset_flags(ctx);
   if (st != FK_OK) return st;
   const int nf = plan.nf, logn = ilog2i(nf), L = 2 * m + 1;
+  if (direct_ok(d, m, T, nq)) {
+    const double2* th = reinterpret_cast<const double2*>(theta);
+    const dim3 grid((unsigned)((nq + DP - 1) / DP), T);
+    if (L <= 40) launch_direct<5>(ctx, d, grid, th, m, nq, dt, Xq, out);
+    else if (L <= 72) launch_direct<9>(ctx, d, grid, th, m, nq, dt, Xq, out);
+    else launch_direct<17>(ctx, d, grid, th, m, nq, dt, Xq, out);
+    FK_HIP(hipGetLastError());
+    return read_flags(ctx);
+  }
   Carve cv(ws, ws_bytes);
   if (d == 2 && predict_nf2(m) == nf) {
     // two pruned FP64 DFTs into padded FP32 grids, then one LDS-resident grid per workgroup
@@ -452,18 +714,10 @@ static fk_status predict_impl(fk_ctx* ctx, const EsPlan& plan, const double* phi
     if (!cv.ok()) return FK_ENOMEM;
     hipLaunchKernelGGL(k_idft_cols, dim3(T * L), dim3(256), 0, ctx->stream, theta, m, nf, phihat, t2);
     hipLaunchKernelGGL(k_idft_rows_pad, dim3(T * nf), dim3(256), 0, ctx->stream, t2, m, nf, W, phihat, pst, gp);
-    int64_t per_chunk = 32768;
-    if ((nq + per_chunk - 1) / per_chunk * T < 2048)
-      per_chunk = std::max<int64_t>(1024, (nq * T + 2047) / 2048);
-    const int64_t nchunk = (nq + per_chunk - 1) / per_chunk;
-    const int64_t nchunk8 = (nchunk + 7) & ~int64_t(7);
-    const int64_t blocks = nchunk8 * T;
-    if (blocks > 0x7fffffff) return FK_EINVAL;
     EsDev2 es{(float)(plan.beta * 1.44269504088896340736), 2.0f / (float)W};
-    const size_t lds = sizeof(float) * pst;
-    FK_W_SWITCH2(W, hipLaunchKernelGGL(k_interp2_lds<WW>, dim3((unsigned)blocks), dim3(1024), lds, ctx->stream, gp,
-                                       pst, nf, T, Xq, dt, nq, per_chunk, nchunk, (double)nf / (2.0 * 3.14159265358979323846),
-                                       es, out, ctx->flags));
+    st = FK_EINVAL;
+    FK_W_SWITCH2(W, st = launch_interp2<WW>(ctx->stream, gp, pst, nf, T, Xq, dt, nq, es, out, ctx->flags));
+    if (st != FK_OK) return st;
     FK_HIP(hipGetLastError());
     return read_flags(ctx);
   }
