@@ -1505,6 +1505,241 @@ __global__ __launch_bounds__(256) void k_bwd2_mfma(const float* __restrict__ A, 
 }
 
 
+// ------------------------------------------------------------------ solves with inverted super-blocks
+// The step-by-step sweeps above are a chain of dependent launches, one per two block columns, each of
+// which must solve its 128 diagonal rows before it can update the others: 34 launches of 6 us per direction
+// at N = 4225 and one lambda, most of it launch and load latency.  Here the 512 x 512 diagonal blocks (SB
+// block columns) are inverted once after the factorization, in place: inv of [[P, 0], [L, Q]] has
+// -inv(Q) L inv(P) below the diagonal, so three doublings of the block size (64 -> 128 -> 256 -> 512), two
+// batched products each, take the 64 x 64 inverses to 512.  A solve step is then two plain products
+// over the whole width of the chip: y_K = inv(L_KK) r_K and r_J -= L_JK y_K for the rows below.
+// FP32 throughout (the panels below the diagonal blocks stay FP16 pairs, as for the sweeps).
+constexpr int SB = 8;   // block columns per super-block
+
+// acc += As Bs, both 64 x 64 row-major in LDS (wave layout of mfma_tile64).
+__device__ __forceinline__ void mfma_tile64_nn(const float* As, const float* Bs, floatx4 acc[2][2]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int r0 = 32 * (w >> 1), c0 = 32 * (w & 1);
+  const int li = lane & 15, lk = lane >> 4;
+#pragma unroll 4
+  for (int k = 0; k < NB; k += 4) {
+    const float a0 = As[(r0 + li) * LDT + k + lk], a1 = As[(r0 + 16 + li) * LDT + k + lk];
+    const float b0 = Bs[(k + lk) * LDT + c0 + li], b1 = Bs[(k + lk) * LDT + c0 + 16 + li];
+    acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b0, acc[0][0], 0, 0, 0);
+    acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b1, acc[0][1], 0, 0, 0);
+    acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b0, acc[1][0], 0, 0, 0);
+    acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b1, acc[1][1], 0, 0, 0);
+  }
+}
+
+// The FP32 inverses of the 64 x 64 diagonal blocks into their place in A (zeros above the diagonal), and
+// the doubling to 128: one workgroup per pair of blocks, -inv(Q) (L inv(P)) with the inner product in LDS.
+__global__ __launch_bounds__(256) void k_inv_pair(float* __restrict__ A, int Np, const float* __restrict__ Linv) {
+  __shared__ __align__(16) float As[NB * LDT];
+  __shared__ __align__(16) float Bs[NB * LDT];
+  const int nb = Np / NB, np = (nb + 1) / 2, p = blockIdx.x % np, l = blockIdx.x / np;
+  const int j = 2 * p, i = j + 1;
+  float* Al = A + (size_t)l * Np * Np;
+  float* dj = Al + (size_t)j * NB * Np + j * NB;
+  const float* Lj = Linv + ((size_t)l * nb + j) * NB * NB;
+  float4 v0, v1, v2, v3;
+  FK_F32_LOAD4(Lj, NB, v0, v1, v2, v3);
+#define FK_PUT(dst)                                                                          \
+  _Pragma("unroll") for (int u_ = 0; u_ < 4; ++u_) {                                         \
+    const int i_ = threadIdx.x + 256 * u_, r_ = i_ / (NB / 4), c_ = (i_ - r_ * (NB / 4)) * 4; \
+    *reinterpret_cast<float4*>((dst) + (size_t)r_ * Np + c_) = u_ == 0 ? v0 : u_ == 1 ? v1 : u_ == 2 ? v2 : v3; \
+  }
+  FK_PUT(dj)
+  if (i >= nb) return;
+  uint32_t* lij = reinterpret_cast<uint32_t*>(Al + (size_t)i * NB * Np + j * NB);
+  uint4 nt0, nt1, nt2, nt3;
+  FK_TILE_FETCH(lij, Np);
+  FK_F32_STORE4(Bs, v0, v1, v2, v3);
+  FK_F32_LOAD4(Lj + NB * NB, NB, v0, v1, v2, v3);
+  FK_TILE_STAGE(As);
+  __syncthreads();
+  floatx4 acc[2][2] = {};
+  mfma_tile64_nn(As, Bs, acc);
+  __syncthreads();
+  store_acc(Bs, LDT, acc, false, 1.f);
+  FK_F32_STORE4(As, v0, v1, v2, v3);
+  FK_PUT(Al + (size_t)i * NB * Np + i * NB)
+#undef FK_PUT
+  __syncthreads();
+  floatx4 acc2[2][2] = {};
+  mfma_tile64_nn(As, Bs, acc2);
+  store_acc(reinterpret_cast<float*>(lij), Np, acc2, false, -1.f);
+}
+
+// One product of a doubling from ht to 2 ht tiles.  A pair's first half is the tiles b0 .. b0 + ht - 1, its
+// second half b0 + ht .. e - 1 (cut at the super-block's or the matrix's end); workgroup: one 64 x 64 tile
+// (i, j), i in the second half, j in the first.
+//   SECOND = false: T(i, j) = sum_{k >= j, first half} L(i, k) Inv(k, j), kept at tile (j, i), above the
+//                   diagonal, where A holds nothing
+//   SECOND = true:  X(i, j) = -sum_{k <= i, second half} Inv(i, k) T(k, j), over L(i, j)
+template <bool SECOND>
+__global__ __launch_bounds__(256) void k_inv_level(float* __restrict__ A, int Np, int ht) {
+  __shared__ __align__(16) float As[NB * LDT];
+  __shared__ __align__(16) float Bs[NB * LDT];
+  const int nb = Np / NB, per = ht * ht;
+  const int pairs_sb = SB / (2 * ht);   // pairs per super-block
+  int b = blockIdx.x;
+  const int t = b % per;
+  b /= per;
+  const int p = b % pairs_sb;
+  b /= pairs_sb;
+  const int nsb = (nb + SB - 1) / SB, sb = b % nsb, l = b / nsb;
+  const int b0 = sb * SB + 2 * ht * p, mid = b0 + ht;
+  const int i = mid + t / ht, j = b0 + t % ht;
+  if (i >= nb) return;
+  float* Al = A + (size_t)l * Np * Np;
+  floatx4 acc[2][2] = {};
+  const int k0 = SECOND ? mid : j, k1 = SECOND ? i + 1 : mid;
+  for (int k = k0; k < k1; ++k) {
+    float4 v0, v1, v2, v3;
+    if constexpr (SECOND) {
+      const float* a = Al + (size_t)i * NB * Np + k * NB;
+      const float* c = Al + (size_t)j * NB * Np + k * NB;   // T(k, j) at tile (j, k)
+      float4 w0, w1, w2, w3;
+      FK_F32_LOAD4(a, Np, v0, v1, v2, v3);
+      FK_F32_LOAD4(c, Np, w0, w1, w2, w3);
+      __syncthreads();
+      FK_F32_STORE4(As, v0, v1, v2, v3);
+      FK_F32_STORE4(Bs, w0, w1, w2, w3);
+    } else {
+      const uint32_t* a = reinterpret_cast<const uint32_t*>(Al + (size_t)i * NB * Np + k * NB);
+      const float* c = Al + (size_t)k * NB * Np + j * NB;
+      uint4 nt0, nt1, nt2, nt3;
+      FK_TILE_FETCH(a, Np);
+      FK_F32_LOAD4(c, Np, v0, v1, v2, v3);
+      __syncthreads();
+      FK_TILE_STAGE(As);
+      FK_F32_STORE4(Bs, v0, v1, v2, v3);
+    }
+    __syncthreads();
+    mfma_tile64_nn(As, Bs, acc);
+  }
+  if constexpr (SECOND)
+    store_acc(Al + (size_t)i * NB * Np + j * NB, Np, acc, false, -1.f);
+  else
+    store_acc(Al + (size_t)j * NB * Np + i * NB, Np, acc, false, 1.f);
+}
+
+// One product of a forward step for 16 rows and all columns: the four waves share the k range, their
+// parts are added in a fixed order.  Lane (li, lk) of a wave holds, per 16 k, the matrix entries of row li
+// at k = 4 lk + e and the vector entries of column li at the same k (e = 0..3, one matrix product each),
+// straight from memory.  K: first row of the super-block, KE: its end.
+//   INV:  out[r] = sum_{k <= r} Inv[r][k] v[k]   r in the super-block
+//   else: out[r] -= sum_k L[r][k] v[k]           r >= KE
+// v and out: [lambda][column][Np].
+template <bool INV>
+__device__ __forceinline__ float tri_entry(uint32_t x) { return INV ? __uint_as_float(x) : split_unpack(x); }
+
+template <bool INV, int NCT>
+__global__ __launch_bounds__(256) void k_tri_fwd(const float* __restrict__ A, int Np, int K, int KE,
+                                                 const float* __restrict__ v, float* __restrict__ out, int ncol) {
+  __shared__ float part[4][16][16 * NCT + 1];
+  const int l = blockIdx.y;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  const int r0 = (INV ? K : KE) + 16 * blockIdx.x;
+  const uint32_t* Al = reinterpret_cast<const uint32_t*>(A) + (size_t)l * Np * Np;
+  const float* vl = v + (size_t)l * ncol * Np;
+  // k range: whole 64-blocks (a diagonal block's zeros are stored), so that a wave's share is a multiple of 16
+  const int len = ((INV ? r0 / NB * NB + NB : KE) - K) / 4, kw = K + w * len;
+  floatx4 acc[NCT];
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct) acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int k = kw; k < kw + len; k += 16) {
+    const uint4 m = *reinterpret_cast<const uint4*>(Al + (size_t)(r0 + li) * Np + k + 4 * lk);
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+      const int t = min(ct * 16 + li, ncol - 1);
+      const float4 b = *reinterpret_cast<const float4*>(vl + (size_t)t * Np + k + 4 * lk);
+      acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(tri_entry<INV>(m.x), b.x, acc[ct], 0, 0, 0);
+      acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(tri_entry<INV>(m.y), b.y, acc[ct], 0, 0, 0);
+      acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(tri_entry<INV>(m.z), b.z, acc[ct], 0, 0, 0);
+      acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(tri_entry<INV>(m.w), b.w, acc[ct], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) part[w][4 * lk + e][ct * 16 + li] = acc[ct][e];
+  __syncthreads();
+  float* ol = out + (size_t)l * ncol * Np;
+#pragma unroll
+  for (int u = 0; u < NCT; ++u) {
+    const int i = threadIdx.x + 256 * u, t = i / 16, r = i % 16;
+    if (t >= ncol) continue;
+    const float s = (part[0][r][t] + part[1][r][t]) + (part[2][r][t] + part[3][r][t]);
+    float* o = ol + (size_t)t * Np + r0 + r;
+    *o = INV ? s : *o - s;
+  }
+}
+
+// The transposed product of a backward step for 64 outputs (columns c of the matrix):
+//   INV:  out[c] = sum_{k >= c} Inv[k][c] v[k]   c in the super-block
+//   else: out[c] -= sum_k L[k][c] v[k]           c < K
+// The eight waves share the 16-row groups of the k range.  A lane reads four consecutive columns 4 li ..
+// of a row (rows whole: 256 contiguous bytes per 16 lanes; one column per lane took 10 us a launch, this
+// 6); entry q of the four is the matrix operand of the product for the columns 4 li + q.
+constexpr int TBW = 8;
+template <bool INV, int NCT>
+__global__ __launch_bounds__(64 * TBW) void k_tri_bwd(const float* __restrict__ A, int Np, int K, int KE,
+                                                      const float* __restrict__ v, float* __restrict__ out, int ncol) {
+  __shared__ float part[TBW][64][16 * NCT + 1];
+  const int l = blockIdx.y;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  const int c0 = (INV ? K : 0) + 64 * blockIdx.x;
+  const uint32_t* Al = reinterpret_cast<const uint32_t*>(A) + (size_t)l * Np * Np + c0 + 4 * li;
+  const float* vl = v + (size_t)l * ncol * Np;
+  const int ka = INV ? c0 : K, groups = (KE - ka) / 16;
+  const int g0 = groups * w / TBW, g1 = groups * (w + 1) / TBW;
+  floatx4 acc[NCT][4];
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[ct][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+  for (int g = g0; g < g1; ++g) {
+    const int k = ka + 16 * g + 4 * lk;
+    uint4 m[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) m[j] = *reinterpret_cast<const uint4*>(Al + (size_t)(k + j) * Np);
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+      const int t = min(ct * 16 + li, ncol - 1);
+      const float4 b = *reinterpret_cast<const float4*>(vl + (size_t)t * Np + k);
+      const float bj[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        acc[ct][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(tri_entry<INV>(m[j].x), bj[j], acc[ct][0], 0, 0, 0);
+        acc[ct][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(tri_entry<INV>(m[j].y), bj[j], acc[ct][1], 0, 0, 0);
+        acc[ct][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(tri_entry<INV>(m[j].z), bj[j], acc[ct][2], 0, 0, 0);
+        acc[ct][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(tri_entry<INV>(m[j].w), bj[j], acc[ct][3], 0, 0, 0);
+      }
+    }
+  }
+  // row 4 lk + e of product q is column 4 (4 lk + e) + q
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) part[w][4 * (4 * lk + e) + q][ct * 16 + li] = acc[ct][q][e];
+  __syncthreads();
+  float* ol = out + (size_t)l * ncol * Np;
+  for (int i = threadIdx.x; i < 64 * ncol; i += 64 * TBW) {
+    const int t = i / 64, c = i % 64;
+    float s = part[0][c][t];
+#pragma unroll
+    for (int u = 1; u < TBW; ++u) s += part[u][c][t];
+    float* o = ol + (size_t)t * Np + c0 + c;
+    *o = INV ? s : *o - s;
+  }
+}
+
 // ------------------------------------------------------------------ FP64 residual
 // Rres[l][t] = Bre[t] - (H64 + lambda_l diag(preal)) X[l][t], for all (l, t) at once:
 // one FP64 GEMM H64 (Np x Np) times X (Np x ncolsTotal), then the diagonal and the
@@ -1596,37 +1831,52 @@ __global__ __launch_bounds__(256) void k_resid64_mfma(const double* __restrict__
   }
 }
 
-// Same residual for a few columns (ncols <= 8): one wave per row streams the row of
-// H64 once (coalesced) against all columns; the tiled kernel above would leave
-// most of each column tile empty.
-constexpr int NARROW = 8;
-__global__ __launch_bounds__(256) void k_resid64_narrow(const double* __restrict__ H, int N, int Np,
-                                                        const double* __restrict__ X, int ncols, int ntgt,
-                                                        int rhs_per_col, const double* __restrict__ Bre,
-                                                        const double* __restrict__ preal,
-                                                        const double* __restrict__ lams, double* __restrict__ Rres) {
-  const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= Np) return;
-  double acc[NARROW];
+// The same residual for up to a few hundred columns, where the tiled kernel has too few tiles for the
+// chip and each walks all of k alone: a workgroup takes 16 rows and 16 NCT columns, its eight waves share
+// k, and their parts are added in a fixed order.  Operands straight from memory: lane (li, lk) holds row
+// (column) li at k = 4 lk + e, e = 0..3, one matrix product each.  Bound by the read of H (147 MB in
+// 46 us at N = 4225, one column); N = 1089: 15 columns 70 -> 5 us, N = 4225: 32 columns 200 -> 60 us.
+// Tiled kernel against this, solve with one refinement step: N = 1089, 24 columns 292 / 176 us, N = 2401,
+// 256 columns 671 / 644, N = 4225, 128 columns 1374 / 1329 and 1024 columns 4531 / 5488.
+constexpr int kRowsCols = 256;
+template <int NCT>
+__global__ __launch_bounds__(512) void k_resid64_rows(const double* __restrict__ H, int N, int Np,
+                                                      const double* __restrict__ X, int ncols, int ntgt,
+                                                      int rhs_per_col, const double* __restrict__ Bre,
+                                                      const double* __restrict__ preal,
+                                                      const double* __restrict__ lams, double* __restrict__ Rres) {
+  __shared__ double part[8][16][16 * NCT + 1];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  const int r0 = blockIdx.x * 16, c0 = blockIdx.y * 16 * NCT;
+  const int groups = Np / 16, g0 = groups * w / 8, g1 = groups * (w + 1) / 8;
+  const double* h = H + (size_t)(r0 + li) * Np + 4 * lk;
+  const double* x[NCT];
 #pragma unroll
-  for (int c = 0; c < NARROW; ++c) acc[c] = 0.0;
-  const double* h = H + (size_t)r * Np;
-  for (int k = lane; k < Np; k += 64) {
-    const double hv = h[k];
+  for (int ct = 0; ct < NCT; ++ct) x[ct] = X + (size_t)min(c0 + 16 * ct + li, ncols - 1) * Np + 4 * lk;
+  doublex4 acc[NCT];
 #pragma unroll
-    for (int c = 0; c < NARROW; ++c)
-      if (c < ncols) acc[c] = fma(hv, X[(size_t)c * Np + k], acc[c]);
+  for (int ct = 0; ct < NCT; ++ct) acc[ct] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+  for (int g = g0; g < g1; ++g) {
+    const doublex4 a = *reinterpret_cast<const doublex4*>(h + 16 * g);
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+      const doublex4 b = *reinterpret_cast<const doublex4*>(x[ct] + 16 * g);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[e], acc[ct], 0, 0, 0);
+    }
   }
 #pragma unroll
-  for (int c = 0; c < NARROW; ++c)
-    for (int o = 32; o > 0; o >>= 1) acc[c] += __shfl_xor(acc[c], o, 64);
-  if (lane < ncols) {
-    const int c = lane;
+  for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[w][lk + 4 * v][16 * ct + li] = acc[ct][v];
+  __syncthreads();
+  for (int i = threadIdx.x; i < 256 * NCT; i += 512) {
+    const int r = r0 + i % 16, cc = i / 16, c = c0 + cc;
+    if (c >= ncols) continue;
     double a = 0.0;
 #pragma unroll
-    for (int cc = 0; cc < NARROW; ++cc)
-      if (cc == c) a = acc[cc];
+    for (int u = 0; u < 8; ++u) a += part[u][i % 16][cc];
     const int l = c / ntgt, t = c - l * ntgt;
     const double xv = X[(size_t)c * Np + r];
     const double ax = a + (r < N ? lams[l] * preal[r] * xv : 0.0);
@@ -1637,9 +1887,16 @@ __global__ __launch_bounds__(256) void k_resid64_narrow(const double* __restrict
 
 static void launch_resid(hipStream_t st, const double* H, int N, int Np, const double* X, int ncols, int ntgt,
                          int rhs_per_col, const double* Bre, const double* preal, const double* lams, double* R) {
-  if (ncols <= NARROW) {
-    hipLaunchKernelGGL(k_resid64_narrow, dim3((Np + 3) / 4), dim3(256), 0, st, H, N, Np, X, ncols, ntgt,
-                       rhs_per_col, Bre, preal, lams, R);
+  if (ncols <= kRowsCols) {
+    const int nct = (ncols + 15) / 16;
+#define FK_ROWS(NCT)                                                                                                \
+  hipLaunchKernelGGL(k_resid64_rows<NCT>, dim3(Np / 16, (nct + NCT - 1) / NCT), dim3(512), 0, st, H, N, Np, X,       \
+                     ncols, ntgt, rhs_per_col, Bre, preal, lams, R)
+    if (nct == 1) FK_ROWS(1);
+    else if (nct == 2) FK_ROWS(2);
+    else if (nct == 3) FK_ROWS(3);
+    else FK_ROWS(4);
+#undef FK_ROWS
     return;
   }
   // Column tile of 32 WN: the one with the fewest tile columns per CU, counting every CU's last
@@ -1836,10 +2093,61 @@ static fk_status factor_all(fk_ctx* ctx, const SolveLayout& s, const DenseShape&
   return FK_OK;
 }
 
+// Whether the solves of this shape go through inverted super-blocks: from three block columns on (two are
+// one launch of the sweeps), and while the inverses, whose cost grows with nb nlam, cost less than the
+// launches they save.  Factor + inverses and solves with one refinement step, sweeps / super-blocks:
+// N = 4225 (nb = 67), 1 lambda and target 1952 / 1562 us, 16 lambdas x 8 targets 5505 / 5116, 64 x 16 16036
+// / 16256; N = 2401, 16 x 16 2104 / 1873; N = 1089 (nb = 18), 5 x 3 656 / 579, 64 x 16 1252 / 1261; N = 289
+// (nb = 5), 1 x 1 166 / 157.
+static bool super_solve(const SolveLayout& s) {
+  const int nb = s.Np / NB;
+  return nb >= 3 && nb * s.nlam <= 1100;
+}
+
+// The super-blocks' inverses, after factor_all.
+static fk_status invert_super(fk_ctx* ctx, const SolveLayout& s) {
+  const int nb = s.Np / NB, nsb = (nb + SB - 1) / SB;
+  hipLaunchKernelGGL(k_inv_pair, dim3((nb + 1) / 2 * s.nlam), dim3(256), 0, ctx->stream, s.A32, s.Np, s.Linv);
+  for (int ht = 2; ht < std::min(SB, nb); ht *= 2) {
+    const dim3 grid(ht * ht * (SB / (2 * ht)) * nsb * s.nlam);
+    hipLaunchKernelGGL(k_inv_level<false>, grid, dim3(256), 0, ctx->stream, s.A32, s.Np, ht);
+    hipLaunchKernelGGL(k_inv_level<true>, grid, dim3(256), 0, ctx->stream, s.A32, s.Np, ht);
+  }
+  FK_HIP(hipGetLastError());
+  return FK_OK;
+}
+
+template <int NCT>
+static void super_steps(fk_ctx* ctx, const SolveLayout& s, float* R, float* Y, float* X) {
+  const int W = SB * NB, nsb = (s.Np + W - 1) / W;
+  for (int k = 0; k < nsb; ++k) {
+    const int K = k * W, KE = std::min(s.Np, K + W);
+    hipLaunchKernelGGL((k_tri_fwd<true, NCT>), dim3((KE - K) / 16, s.nlam), dim3(256), 0, ctx->stream, s.A32, s.Np, K,
+                       KE, R, Y, s.ntgt);
+    if (KE < s.Np)
+      hipLaunchKernelGGL((k_tri_fwd<false, NCT>), dim3((s.Np - KE) / 16, s.nlam), dim3(256), 0, ctx->stream, s.A32,
+                         s.Np, K, KE, Y, R, s.ntgt);
+  }
+  for (int k = nsb - 1; k >= 0; --k) {
+    const int K = k * W, KE = std::min(s.Np, K + W);
+    hipLaunchKernelGGL((k_tri_bwd<true, NCT>), dim3((KE - K) / 64, s.nlam), dim3(64 * TBW), 0, ctx->stream, s.A32,
+                       s.Np, K, KE, Y, X, s.ntgt);
+    if (K > 0)
+      hipLaunchKernelGGL((k_tri_bwd<false, NCT>), dim3(K / 64, s.nlam), dim3(64 * TBW), 0, ctx->stream, s.A32, s.Np, K,
+                         KE, X, Y, s.ntgt);
+  }
+}
+
 // D32 = A^-1 R32 per lambda (ncol = ntgt columns each), through Y32.
 static fk_status trsm_all(fk_ctx* ctx, const SolveLayout& s, const DenseShape& sh, float* R, float* Y, float* X) {
   const int nb = s.Np / NB;
   const bool two = s.ntgt > 16;
+  if (super_solve(s)) {
+    if (two) super_steps<2>(ctx, s, R, Y, X);
+    else super_steps<1>(ctx, s, R, Y, X);
+    FK_HIP(hipGetLastError());
+    return FK_OK;
+  }
   // workgroups per lambda: about sh.trsm_wg in all, each sweeping several rows
   const int gmax = std::max(1, sh.trsm_wg / s.nlam);
   // two block columns per launch (the last one alone when nb is odd)
@@ -2041,6 +2349,7 @@ static fk_status tune_dense(fk_ctx* ctx, const SolveLayout& s, DenseShape* out, 
   FK_HIP(hipMemsetAsync(s.R32, 0, sizeof(float) * nv, ctx->stream));
   float best_t = 0.f;
   for (int wg : {512, 768, 256, 1024}) {
+    if (super_solve(s)) break;   // no sweeps to tune
     DenseShape c = sh;
     c.trsm_wg = wg;
     FK_HIP(hipEventRecord(e0, ctx->stream));
@@ -2102,6 +2411,10 @@ fk_status solve_impl(fk_ctx* ctx, const SolveProblem& P, const SolveLayout& s, d
   FK_HIP(hipEventRecord(ev[6], ctx->stream));
   if (!factored) {
     st = factor_all(ctx, s, sh);
+    if (st != FK_OK) return st;
+  }
+  if (super_solve(s)) {
+    st = invert_super(ctx, s);
     if (st != FK_OK) return st;
   }
   FK_HIP(hipEventRecord(ev[7], ctx->stream));
