@@ -191,6 +191,17 @@ fk_status sort2(hipStream_t st, const void* X, fk_dtype dt, int64_t n, int64_t x
                 int nf, int fb, int W, double scale, int tshift, int nbx, const T1Shape& shape, Sort2Bufs b,
                 uint32_t* totals, uint32_t* crd, uint32_t* wts, uint64_t* start, int* flags);
 
+// The same for the 3-D stage: records of 3 + nw words in the order of the bins of 8^3 window-start cells,
+// bin starts in start[0 .. (nf / 8)^3].
+bool sort3_ok(int nf, int64_t n, int nw);
+void sort3_carve(Carve& cv, int64_t n, int nf, int nw, Sort2Bufs* b);
+fk_status sort3(hipStream_t st, const void* X, fk_dtype dt, int64_t n, int64_t xstride, const void* Y, int nw, int nf,
+                int fb, int W, double scale, const Sort2Bufs& b, uint32_t* rec, uint64_t* start, int* flags);
+
+// 3-D spread of the sorted records (spread3.hip) into the FP64 grid [nw + 1][nf]^3.
+fk_status launch_spread3(hipStream_t st, int W, const uint32_t* rec, int nw, const uint64_t* start, int nf, int fb,
+                         double beta, int64_t n, double* grid);
+
 }  // namespace fk
 
 struct fk_ctx {

@@ -219,7 +219,7 @@ __global__ __launch_bounds__(1024) void k_s2_scan1(uint32_t* __restrict__ cnt, i
 // Workgroup `blk` of the second pass: its row and its part [q0, q1) of the row's points.  A row of len
 // points has ceil(len / slice_pts) slices of equal size, so the work is even for any density; the grid
 // holds one workgroup per row more than n / slice_pts.  False past the last slice.
-__device__ __forceinline__ bool slice_of(const uint64_t* __restrict__ start1, int nbx, uint32_t slice_pts,
+__device__ __forceinline__ bool slice_of(const uint64_t* __restrict__ start1, int nrow, uint32_t slice_pts,
                                          uint32_t blk, int* row, uint64_t* q0, uint64_t* q1) {
   __shared__ uint32_t found[4];
   static_assert(KMAX % 64 == 0, "rows per lane");
@@ -230,7 +230,7 @@ __device__ __forceinline__ bool slice_of(const uint64_t* __restrict__ start1, in
 #pragma unroll
     for (int i = 0; i < RP; ++i) {
       const int r = lane * RP + i;
-      const uint32_t len = r < nbx ? (uint32_t)(start1[r + 1] - start1[r]) : 0u;
+      const uint32_t len = r < nrow ? (uint32_t)(start1[r + 1] - start1[r]) : 0u;
       ns[i] = len / slice_pts + (len % slice_pts != 0);
       sum += ns[i];
     }
@@ -347,11 +347,11 @@ __global__ __launch_bounds__(BT) void k_s2_count2(const uint2* __restrict__ crd1
 }
 
 // Offsets of pass 2 (in place of its counts), one workgroup per row: cnt2[slice][by] becomes the position
-// at which the slice's points of bin (row, by) start, in the order of the slices, and start[row nbx + by]
-// the bin's start.  A row's slices are consecutive workgroups of the second pass; thread (g, by) takes
+// at which the slice's points of bin (row, by) start, in the order of the slices, and start[row ncol + by]
+// the bin's start (ncol buckets per row).  A row's slices are consecutive workgroups of the second pass; thread (g, by) takes
 // the g-th part of them.
 __global__ __launch_bounds__(1024) void k_s2_scan2(uint32_t* __restrict__ cnt2, const uint64_t* __restrict__ start1,
-                                                   uint32_t slice_pts, int nbx, uint64_t* __restrict__ start) {
+                                                   uint32_t slice_pts, int ncol, uint64_t* __restrict__ start) {
   __shared__ uint32_t sh[16];
   __shared__ uint32_t part[1024], tot[KMAX];
   const int row = blockIdx.x, t = threadIdx.x;
@@ -362,40 +362,40 @@ __global__ __launch_bounds__(1024) void k_s2_scan2(uint32_t* __restrict__ cnt2, 
   uint32_t first;   // slices of the rows before
   (void)block_scan(t < row ? slices(t) : 0u, sh, &first);
   const uint32_t ns = slices(row);
-  const int groups = 1024 / nbx, by = t % nbx, g = t / nbx;   // threads past groups nbx idle
+  const int groups = 1024 / ncol, by = t % ncol, g = t / ncol;   // threads past groups ncol idle
   const bool on = g < groups;
   const uint32_t s0 = (uint32_t)((uint64_t)ns * g / groups), s1 = (uint32_t)((uint64_t)ns * (g + 1) / groups);
-  uint32_t* c = cnt2 + (int64_t)first * nbx + by;
+  uint32_t* c = cnt2 + (int64_t)first * ncol + by;
   uint32_t sum = 0;
   if (on) {
 #pragma unroll 4
-    for (uint32_t s = s0; s < s1; ++s) sum += c[(int64_t)s * nbx];
+    for (uint32_t s = s0; s < s1; ++s) sum += c[(int64_t)s * ncol];
   }
   part[t] = sum;
   __syncthreads();
   uint32_t before = 0, all = 0;   // the bin's points in earlier groups, and in all
   if (on)
     for (int i = 0; i < groups; ++i) {
-      const uint32_t v = part[i * nbx + by];
+      const uint32_t v = part[i * ncol + by];
       before += i < g ? v : 0u;
       all += v;
     }
-  if (t < nbx) tot[by] = all;
+  if (t < ncol) tot[by] = all;
   uint32_t total;
-  const uint32_t pre = block_scan(t < nbx ? all : 0u, sh, &total);
+  const uint32_t pre = block_scan(t < ncol ? all : 0u, sh, &total);
   const uint32_t base = (uint32_t)start1[row];
-  if (t < nbx) {
-    start[(int64_t)row * nbx + t] = base + pre;
+  if (t < ncol) {
+    start[(int64_t)row * ncol + t] = base + pre;
     tot[t] = base + pre;
-    if (t == 0 && row == nbx - 1) start[(int64_t)nbx * nbx] = (uint64_t)base + total;
+    if (t == 0 && row == (int)gridDim.x - 1) start[(int64_t)gridDim.x * ncol] = (uint64_t)base + total;
   }
   __syncthreads();
   if (on) {
     uint32_t run = tot[by] + before;
 #pragma unroll 4
     for (uint32_t s = s0; s < s1; ++s) {
-      const uint32_t v = c[(int64_t)s * nbx];
-      c[(int64_t)s * nbx] = run;
+      const uint32_t v = c[(int64_t)s * ncol];
+      c[(int64_t)s * ncol] = run;
       run += v;
     }
   }
@@ -635,6 +635,211 @@ __global__ __launch_bounds__(BT) void k_s2n_scatter2(const uint2* __restrict__ c
 #undef FK_FETCH2N
 }
 
+// ---------------------------------------------------------------- three dimensions
+// The same two passes for the 3-D stage: bins of 8^3 window-start cells, numbered (bx nbx + by) nbx + bz (at
+// most 2^15 of them); the first pass orders by the upper half of the bin number, the second by the lower
+// half.  Records of R = 3 + nw words (fixed-point coordinates, weights), staged word by word.
+struct Bin3 {
+  uint32_t wbias;
+  int fb, nf, nbx, lo;   // lo: bits of the second pass
+  __device__ int operator()(const uint32_t* U) const {
+    int b = 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) b = b * nbx + window_bin(U[a], fb, wbias, nf, 3);
+    return b;
+  }
+};
+
+template <int R>
+constexpr int ppt3() { return R <= 4 ? 4 : (R <= 8 ? 2 : 1); }
+
+template <int R>
+struct Stage3 {
+  static constexpr int NPT = ppt3<R>();
+  uint32_t cur[KMAX], hist[KMAX], lofs[KMAX];
+  uint32_t total;
+  uint8_t sbin[BT * NPT];
+  uint32_t rec[BT * NPT * R];
+};
+
+template <typename TX>
+__global__ __launch_bounds__(BT) void k_s3_count1(const TX* __restrict__ X, int64_t n, int64_t xstride, double scale,
+                                                  uint32_t nf_fix, Bin3 bin, int nk, int64_t chunk,
+                                                  uint32_t* __restrict__ cnt, uint32_t* __restrict__ rowtot, int* flags) {
+  __shared__ uint32_t hist[KMAX];
+  for (int i = threadIdx.x; i < nk; i += BT) hist[i] = 0;
+  __syncthreads();
+  const int64_t beg = (int64_t)blockIdx.x * chunk, end = min(n, beg + chunk);
+  for (int64_t j0 = beg + threadIdx.x; j0 < end; j0 += (int64_t)CU1 * BT) {
+    double x[CU1][3];
+#pragma unroll
+    for (int u = 0; u < CU1; ++u) {
+      const int64_t jc = min(j0 + (int64_t)u * BT, end - 1);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) x[u][a] = (double)X[a * xstride + jc];
+    }
+#pragma unroll
+    for (int u = 0; u < CU1; ++u) {
+      if (j0 + (int64_t)u * BT >= end) break;
+      uint32_t U[3];
+      bool ok = true;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) ok = to_fixed(x[u][a], scale, nf_fix, &U[a], flags) && ok;
+      if (ok) atomicAdd(&hist[bin(U) >> bin.lo], 1u);
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < nk; i += BT) {
+    cnt[(int64_t)blockIdx.x * nk + i] = hist[i];
+    if (hist[i]) atomicAdd(&rowtot[i], hist[i]);
+  }
+}
+
+template <int R>
+__device__ __forceinline__ void write_batch3(Stage3<R>& sm, uint32_t* __restrict__ out) {
+  const uint32_t words = sm.total * R;
+  for (uint32_t q = threadIdx.x; q < words; q += BT) {
+    const uint32_t s = q / R;
+    const int b = sm.sbin[s];
+    out[((size_t)sm.cur[b] + (s - sm.lofs[b])) * R + q % R] = sm.rec[q];
+  }
+}
+
+template <typename TX, int R>
+__global__ __launch_bounds__(BT) void k_s3_scatter1(const TX* __restrict__ X, int64_t n, int64_t xstride,
+                                                    const TX* __restrict__ Y, double scale, uint32_t nf_fix, Bin3 bin,
+                                                    int nk, int64_t chunk, const uint32_t* __restrict__ off,
+                                                    uint32_t* __restrict__ rec1, int* flags) {
+  constexpr int NPT = ppt3<R>(), NW = R - 3;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  Stage3<R>& sm = *reinterpret_cast<Stage3<R>*>(smem_raw);
+  const int tid = threadIdx.x;
+  for (int b = tid; b < nk; b += BT) {
+    sm.cur[b] = off[(int64_t)blockIdx.x * nk + b];
+    sm.hist[b] = 0;
+  }
+  __syncthreads();
+  const int64_t beg = (int64_t)blockIdx.x * chunk, end = min(n, beg + chunk);
+  for (int64_t base = beg; base < end; base += (int64_t)BT * NPT) {
+    double x[NPT][3];
+    float w[NPT][NW > 0 ? NW : 1];
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+      const int64_t jc = min(base + u * BT + tid, end - 1);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) x[u][a] = (double)X[a * xstride + jc];
+#pragma unroll
+      for (int c = 0; c < NW; ++c) w[u][c] = (float)Y[(int64_t)c * n + jc];
+    }
+    uint32_t U[NPT][3], rank[NPT];
+    int key[NPT];
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+      bool ok = base + u * BT + tid < end;
+      if (ok) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) ok = to_fixed(x[u][a], scale, nf_fix, &U[u][a], flags) && ok;
+      }
+      key[u] = ok ? bin(U[u]) >> bin.lo : -1;
+      rank[u] = ok ? atomicAdd(&sm.hist[key[u]], 1u) : 0u;
+    }
+    scan_counts(sm, nk);
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+      if (key[u] < 0) continue;
+      const uint32_t s = sm.lofs[key[u]] + rank[u];
+      sm.sbin[s] = (uint8_t)key[u];
+      uint32_t* r = sm.rec + s * R;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) r[a] = U[u][a];
+#pragma unroll
+      for (int c = 0; c < NW; ++c) {
+        float wc = w[u][c];
+        if (!(wc == wc) || isinf(wc)) {
+          atomicOr(&flags[kFlagNaN], 1);
+          wc = 0.f;
+        }
+        r[3 + c] = __float_as_uint(wc);
+      }
+    }
+    __syncthreads();
+    write_batch3(sm, rec1);
+    advance_cursors(sm, nk);
+  }
+}
+
+template <int R>
+__global__ __launch_bounds__(BT) void k_s3_count2(const uint32_t* __restrict__ rec1, const uint64_t* __restrict__ start1,
+                                                  int nrow, uint32_t slice_pts, Bin3 bin, uint32_t* __restrict__ cnt2) {
+  __shared__ uint32_t hist[KMAX];
+  const int nk = 1 << bin.lo;
+  for (int i = threadIdx.x; i < nk; i += BT) hist[i] = 0;
+  int row;
+  uint64_t q0, q1;
+  if (!slice_of(start1, nrow, slice_pts, blockIdx.x, &row, &q0, &q1)) return;
+  for (uint64_t p = q0 + threadIdx.x; p < q1; p += (uint64_t)CU1 * BT) {
+    uint32_t U[CU1][3];
+#pragma unroll
+    for (int u = 0; u < CU1; ++u) {
+      const uint32_t* r = rec1 + min(p + (uint64_t)u * BT, q1 - 1) * R;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) U[u][a] = r[a];
+    }
+#pragma unroll
+    for (int u = 0; u < CU1; ++u)
+      if (p + (uint64_t)u * BT < q1) atomicAdd(&hist[bin(U[u]) & (nk - 1)], 1u);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < nk; i += BT) cnt2[(int64_t)blockIdx.x * nk + i] = hist[i];
+}
+
+template <int R>
+__global__ __launch_bounds__(BT) void k_s3_scatter2(const uint32_t* __restrict__ rec1,
+                                                    const uint64_t* __restrict__ start1, int nrow,
+                                                    const uint32_t* __restrict__ off2, uint32_t slice_pts, Bin3 bin,
+                                                    uint32_t* __restrict__ rec) {
+  constexpr int NPT = ppt3<R>();
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  Stage3<R>& sm = *reinterpret_cast<Stage3<R>*>(smem_raw);
+  const int tid = threadIdx.x, nk = 1 << bin.lo;
+  int row;
+  uint64_t q0, q1;
+  if (!slice_of(start1, nrow, slice_pts, blockIdx.x, &row, &q0, &q1)) return;
+  for (int b = tid; b < nk; b += BT) {
+    sm.cur[b] = off2[(int64_t)blockIdx.x * nk + b];
+    sm.hist[b] = 0;
+  }
+  __syncthreads();
+  for (uint64_t base = q0; base < q1; base += (uint64_t)BT * NPT) {
+    uint32_t v[NPT][R], rank[NPT];
+    int key[NPT];
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+      const uint32_t* r = rec1 + min(base + (uint64_t)u * BT + tid, q1 - 1) * R;
+#pragma unroll
+      for (int c = 0; c < R; ++c) v[u][c] = r[c];
+    }
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+      const bool ok = base + (uint64_t)u * BT + tid < q1;
+      key[u] = ok ? bin(v[u]) & (nk - 1) : -1;
+      rank[u] = ok ? atomicAdd(&sm.hist[key[u]], 1u) : 0u;
+    }
+    scan_counts(sm, nk);
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+      if (key[u] < 0) continue;
+      const uint32_t s = sm.lofs[key[u]] + rank[u];
+      sm.sbin[s] = (uint8_t)key[u];
+#pragma unroll
+      for (int c = 0; c < R; ++c) sm.rec[s * R + c] = v[u][c];
+    }
+    __syncthreads();
+    write_batch3(sm, rec);
+    advance_cursors(sm, nk);
+  }
+}
+
 struct Sort2Geom {
   int nblk1;            // workgroups of the first pass
   int64_t chunk1;       // their points
@@ -642,13 +847,12 @@ struct Sort2Geom {
   int nblk2;            // its workgroups: every row's last slice may be short
 };
 
-// First pass: up to blk workgroups of at least 8192 points (two staged batches of narrow records; a
-// workgroup of 65536, the earlier minimum, left 1e7 points to 152 of the 256 CUs and 30011 to one: 97 and
-// 98 us for the scatter against 61 and 27).  Second pass: slices of slice_pts points, smaller ones
-// where n would not give 512 of them.
+// First pass: up to blk workgroups of at least 2048 points (65536, the earlier minimum, left 1e7 points to
+// 152 of the 256 CUs and 30011 to one workgroup: 97 and 98 us for the scatter against 61 and 10).  Second
+// pass: slices of slice_pts points, smaller ones where n would not give 512 of them.
 Sort2Geom sort2_geom(int64_t n, int nbx, int blk, int64_t slice_pts) {
   Sort2Geom g;
-  g.nblk1 = (int)std::min<int64_t>(blk, std::max<int64_t>(1, (n + 8191) / 8192));
+  g.nblk1 = (int)std::min<int64_t>(blk, std::max<int64_t>(1, (n + 2047) / 2048));
   g.chunk1 = (n + g.nblk1 - 1) / g.nblk1;
   g.slice_pts = (uint32_t)std::max<int64_t>(4096, std::min<int64_t>(slice_pts, n / 512));
   g.nblk2 = (int)(nbx + n / g.slice_pts);
@@ -722,6 +926,45 @@ fk_status sort2_typed(const SortArgs& a, const TX* X, const TX* Y, const Sort2Ge
   return hipGetLastError() == hipSuccess ? FK_OK : FK_EHIP;
 }
 
+template <typename TX, int R>
+void sort3_run(const SortArgs& a, const TX* X, const TX* Y, const Sort2Geom& g, const Sort2Bufs& b, const Bin3& bin,
+               int nrow, uint32_t* rec) {
+  const int ncol = 1 << bin.lo;
+  hipLaunchKernelGGL(k_s3_count1<TX>, dim3(g.nblk1), dim3(BT), 0, a.st, X, a.n, a.xstride, a.scale, a.nf_fix, bin, nrow,
+                     g.chunk1, b.cnt1, b.rowtot, a.flags);
+  hipLaunchKernelGGL(k_s2_scan1, dim3(nrow), dim3(1024), 0, a.st, b.cnt1, nrow, g.nblk1, b.rowtot, b.start1);
+  hipLaunchKernelGGL((k_s3_scatter1<TX, R>), dim3(g.nblk1), dim3(BT), sizeof(Stage3<R>), a.st, X, a.n, a.xstride, Y,
+                     a.scale, a.nf_fix, bin, nrow, g.chunk1, b.cnt1, b.crd1, a.flags);
+  hipLaunchKernelGGL(k_s3_count2<R>, dim3(g.nblk2), dim3(BT), 0, a.st, b.crd1, b.start1, nrow, g.slice_pts, bin, b.cnt2);
+  hipLaunchKernelGGL(k_s2_scan2, dim3(nrow), dim3(1024), 0, a.st, b.cnt2, b.start1, g.slice_pts, ncol, a.start);
+  hipLaunchKernelGGL(k_s3_scatter2<R>, dim3(g.nblk2), dim3(BT), sizeof(Stage3<R>), a.st, b.crd1, b.start1, nrow, b.cnt2,
+                     g.slice_pts, bin, rec);
+}
+
+template <typename TX>
+fk_status sort3_typed(const SortArgs& a, const TX* X, const TX* Y, const Sort2Geom& g, const Sort2Bufs& b,
+                      const Bin3& bin, int nrow, uint32_t* rec) {
+  switch (a.nw) {
+    case 0: sort3_run<TX, 3>(a, X, Y, g, b, bin, nrow, rec); break;
+    case 1: sort3_run<TX, 4>(a, X, Y, g, b, bin, nrow, rec); break;
+    case 2: sort3_run<TX, 5>(a, X, Y, g, b, bin, nrow, rec); break;
+    case 3: sort3_run<TX, 6>(a, X, Y, g, b, bin, nrow, rec); break;
+    case 4: sort3_run<TX, 7>(a, X, Y, g, b, bin, nrow, rec); break;
+    case 5: sort3_run<TX, 8>(a, X, Y, g, b, bin, nrow, rec); break;
+    case 6: sort3_run<TX, 9>(a, X, Y, g, b, bin, nrow, rec); break;
+    case 7: sort3_run<TX, 10>(a, X, Y, g, b, bin, nrow, rec); break;
+    case 8: sort3_run<TX, 11>(a, X, Y, g, b, bin, nrow, rec); break;
+    default: return FK_EINVAL;
+  }
+  return hipGetLastError() == hipSuccess ? FK_OK : FK_EHIP;
+}
+
+int sort3_bits(int nbx) {
+  int b = 0;
+  while ((1 << b) < nbx) ++b;
+  return 3 * b;
+}
+
 }  // namespace
 
 bool sort2_ok(int nbx) { return nbx >= 1 && nbx <= KMAX; }
@@ -761,6 +1004,35 @@ fk_status sort2(hipStream_t st, const void* X, fk_dtype dt, int64_t n, int64_t x
   if (dt == FK_F64)
     return sort2_typed(a, static_cast<const double*>(X), static_cast<const double*>(Y), g, b, crd, wts);
   return sort2_typed(a, static_cast<const float*>(X), static_cast<const float*>(Y), g, b, crd, wts);
+}
+
+bool sort3_ok(int nf, int64_t n, int nw) {
+  return nf >= 16 && (nf & (nf - 1)) == 0 && sort3_bits(nf / 8) <= 15 && n <= (int64_t)0xffffffff && nw <= 8;
+}
+
+void sort3_carve(Carve& cv, int64_t n, int nf, int nw, Sort2Bufs* b) {
+  const int bits = sort3_bits(nf / 8), lo = bits / 2, nrow = 1 << (bits - lo);
+  const Sort2Geom g = sort2_geom(n, nrow, kSortBlkMax, kSortSliceMin);
+  b->rowtot = cv.take<uint32_t>((size_t)nrow);
+  b->cnt1 = cv.take<uint32_t>((size_t)g.nblk1 * nrow);
+  b->start1 = cv.take<uint64_t>((size_t)nrow + 1);
+  b->cnt2 = cv.take<uint32_t>((size_t)g.nblk2 << lo);
+  b->crd1 = cv.take<uint32_t>((size_t)n * (3 + nw));
+}
+
+fk_status sort3(hipStream_t st, const void* X, fk_dtype dt, int64_t n, int64_t xstride, const void* Y, int nw, int nf,
+                int fb, int W, double scale, const Sort2Bufs& b, uint32_t* rec, uint64_t* start, int* flags) {
+  if (!sort3_ok(nf, n, nw)) return FK_EINVAL;
+  const int bits = sort3_bits(nf / 8), lo = bits / 2, nrow = 1 << (bits - lo);
+  const Sort2Geom g = sort2_geom(n, nrow, 512, 65536);
+  const uint32_t one = 1u << fb;
+  const uint32_t wbias = (one - 1u) + 8u * one - ((uint32_t)W << (fb - 1));
+  const Bin3 bin{wbias, fb, nf, nf / 8, lo};
+  const SortArgs a{st, n, xstride, nw, nf, fb, 3, nf / 8, (uint32_t)nf << fb, wbias, scale, start, flags};
+  FK_HIP(hipMemsetAsync(b.rowtot, 0, sizeof(uint32_t) * nrow, st));
+  if (dt == FK_F64)
+    return sort3_typed(a, static_cast<const double*>(X), static_cast<const double*>(Y), g, b, bin, nrow, rec);
+  return sort3_typed(a, static_cast<const float*>(X), static_cast<const float*>(Y), g, b, bin, nrow, rec);
 }
 
 }  // namespace fk
