@@ -96,7 +96,11 @@ extern "C" const char* fk_status_string(fk_status s) {
 
 namespace fk {
 
+// The flags are set to their initial values unless the last call that read them back found them so.
 fk_status reset_flags(fk_ctx* ctx) {
+  const bool clean = ctx->flags_clean;
+  ctx->flags_clean = false;   // until this call's flags are read back
+  if (clean) return FK_OK;
   int init[kFlagCount] = {0, 0, 0, 0x7fffffff, 0, 0x7fffffff, 0, 0};
   std::memcpy(ctx->flags_host, init, sizeof(init));
   FK_HIP(hipMemcpyAsync(ctx->flags, ctx->flags_host, sizeof(init), hipMemcpyHostToDevice, ctx->stream));
@@ -140,7 +144,9 @@ fk_status read_flags(fk_ctx* ctx) {
   return flag_status(ctx);
 }
 
-fk_status flag_status(const fk_ctx* ctx) {
+fk_status flag_status(fk_ctx* ctx) {
+  // (a value behind the three is written only together with one of them)
+  ctx->flags_clean = !ctx->flags_host[kFlagNaN] && !ctx->flags_host[kFlagRange] && !ctx->flags_host[kFlagNotPD];
   if (ctx->flags_host[kFlagNaN]) return FK_ENAN;
   if (ctx->flags_host[kFlagRange]) return FK_ERANGE;
   if (ctx->flags_host[kFlagNotPD]) return FK_ENOTPD;

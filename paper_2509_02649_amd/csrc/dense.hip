@@ -24,6 +24,7 @@
 
 #include <cmath>
 #include <cstdio>
+#include <cstring>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -150,20 +151,6 @@ __device__ double real_entry(const Q& q, int r, int s, int L) {
 struct ToeplitzQ {
   const double* M;
   int m, d;
-  __device__ cplx operator()(int i, int j) const {
-    const int L = 2 * m + 1, G = 4 * m + 1;
-    int idx = 0;
-    int ii = i, jj = j;
-    int mul = 1;
-    for (int a = d - 1; a >= 0; --a) {
-      int ki = ii % L - m, kj = jj % L - m;
-      ii /= L;
-      jj /= L;
-      idx += (kj - ki + 2 * m) * mul;
-      mul *= G;
-    }
-    return {M[2 * idx], M[2 * idx + 1]};
-  }
   // Linear offset of mode i in the generator grid (sum over axes of k_a G^a): the entry (i, j) is at
   // off(j) - off(i) + centre, so four entries of one real-form element need four decodes, not eight.
   __device__ int off(int i) const {
@@ -215,16 +202,17 @@ struct PdeQ {
     // (e^{iqhi} - e^{iqlo}) / (iq) = ((s1 - s0) - i (c1 - c0)) / q
     return {(s1 - s0) / q, -(c1 - c0) / q};
   }
-  __device__ cplx operator()(int i, int j) const {
+  // entry (i, j) with the box integrals of axis a at boxt[a G + (l_a - k_a) + 2m], G = 4m + 1
+  __device__ cplx entry(int i, int j, const cplx* boxt, int G) const {
     const int L = 2 * m + 1;
     cplx C;
     if (d == 1) {
-      C = box((j - m) - (i - m), lo0, hi0);
+      C = boxt[(j - m) - (i - m) + 2 * m];
       const double s = 1.0 / (2.0 * kPi);
       C = {C.re * s, C.im * s};
     } else {
       const int k0 = i / L - m, k1 = i % L - m, l0 = j / L - m, l1 = j % L - m;
-      const cplx c0 = box(l0 - k0, lo0, hi0), c1 = box(l1 - k1, lo1, hi1);
+      const cplx c0 = boxt[l0 - k0 + 2 * m], c1 = boxt[G + l1 - k1 + 2 * m];
       const double s = 1.0 / (4.0 * kPi * kPi);
       C = {(c0.re * c1.re - c0.im * c1.im) * s, (c0.re * c1.im + c0.im * c1.re) * s};
     }
@@ -245,32 +233,78 @@ struct DenseQ {
   }
 };
 
-template <class Q1, class Q2>
-struct SumQ {
-  Q1 a;
-  Q2 b;
-  __device__ cplx operator()(int i, int j) const { return cadd(a(i, j), b(i, j)); }
-};
-
-// H64[r][s] = real form of Q (r, s < N); zero padding up to Np.
+// H64[r][s] = real form of Q (r, s < N); zero padding up to Np.  Any block structure (L modes per block).
 template <class Q>
 __global__ __launch_bounds__(256) void k_assemble_real(Q q, int N, int L, int Np, double* __restrict__ H) {
   int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (int64_t)Np * Np) return;
   int r = (int)(idx / Np), s = (int)(idx - (int64_t)r * Np);
-  double v = 0.0;
-  if (r < N && s < N) {
-    if constexpr (std::is_same<Q, ToeplitzQ>::value) {
-      int tr, k, nk, ts, l, nl;
-      real_to_complex(r, L, &tr, &k, &nk);
-      real_to_complex(s, L, &ts, &l, &nl);
-      const ToeplitzPairQ pq{q.M, q.centre(), k, l, q.off(k), q.off(nk), q.off(l), q.off(nl)};
-      v = real_entry(pq, r, s, L);
-    } else {
-      v = real_entry(q, r, s, L);
+  H[idx] = r < N && s < N ? real_entry(q, r, s, L) : 0.0;
+}
+
+// The same for one block of N modes (N odd) with a Toeplitz part: rows 2g - 1 and 2g are the cosine and the
+// sine of one pair of modes +-k, so the 2 x 2 entries of a pair of rows and a pair of columns come from the
+// same four complex entries.  A thread computes such a block (rows and columns past N: zeros): a quarter of the
+// index arithmetic, of the generator reads and, with the physics-informed part, of the box integrals (which
+// come from a table per axis here, boxt[q + 2m], filled by the workgroup: they depend on k - l only).
+// Toeplitz, N = 4225: 146 us -> 42 (143 MB written); with the heat penalty, N = 1681: 177 -> 22 us.
+template <bool PDE>
+__global__ __launch_bounds__(256) void k_assemble_pairs(ToeplitzQ tq, PdeQ pq, int N, int Np, double* __restrict__ H) {
+  extern __shared__ cplx boxt[];
+  const int G = 4 * tq.m + 1;
+  if constexpr (PDE) {
+    for (int i = threadIdx.x; i < G * pq.d; i += 256) {
+      const int ax = i / G, q = i - ax * G - 2 * tq.m;
+      boxt[i] = PdeQ::box(q, ax == 0 ? pq.lo0 : pq.lo1, ax == 0 ? pq.hi0 : pq.hi1);
     }
+    __syncthreads();
   }
-  H[idx] = v;
+  const int gc = blockIdx.x * 256 + threadIdx.x, gr = blockIdx.y;   // groups 0 .. Np / 2
+  if (gc > Np / 2) return;
+  const int h = (N - 1) / 2, c0 = h;   // group g <= h: modes c0 + g and c0 - g
+  const bool in = gr <= h && gc <= h;
+  const int k = c0 + gr, nk = c0 - gr, l = c0 + gc, nl = c0 - gc;
+  cplx kl{0, 0}, knl{0, 0}, nkl{0, 0}, nknl{0, 0};
+  if (in) {
+    const ToeplitzPairQ t{tq.M, tq.centre(), k, l, tq.off(k), tq.off(nk), tq.off(l), tq.off(nl)};
+    auto at = [&](int i, int j) -> cplx {
+      cplx v = t(i, j);
+      if constexpr (PDE) v = cadd(v, pq.entry(i, j, boxt, G));
+      return v;
+    };
+    kl = at(k, l);
+    knl = gc ? at(k, nl) : kl;
+    nkl = gr ? at(nk, l) : kl;
+    nknl = gr ? (gc ? at(nk, nl) : nkl) : knl;
+  }
+  const double rs2 = 0.70710678118654752440;
+  auto put = [&](int r, int c, double v) {
+    if (r >= 0 && r < Np && c >= 0 && c < Np) H[(size_t)r * Np + c] = in ? v : 0.0;
+  };
+  const int r1 = 2 * gr - 1, s1 = 2 * gc - 1;   // cosine rows and columns; sine: + 1; the constant: 0 = 2 * 0
+  if (gr == 0 && gc == 0) {
+    put(0, 0, kl.re);
+  } else if (gr == 0) {
+    put(0, s1, (kl.re + knl.re) * rs2);
+    put(0, s1 + 1, -(knl.im - kl.im) * rs2);
+  } else if (gc == 0) {
+    put(r1, 0, (kl.re + nkl.re) * rs2);
+    put(r1 + 1, 0, (nkl.im - kl.im) * rs2);
+  } else {
+    put(r1, s1, 0.5 * (kl.re + knl.re + nkl.re + nknl.re));
+    put(r1, s1 + 1, -0.5 * csub(cadd(knl, nknl), cadd(kl, nkl)).im);
+    put(r1 + 1, s1, 0.5 * csub(cadd(nkl, nknl), cadd(kl, knl)).im);
+    put(r1 + 1, s1 + 1, 0.5 * (nknl.re - nkl.re - knl.re + kl.re));
+  }
+}
+
+static void launch_assemble_pairs(hipStream_t st, const ToeplitzQ& tq, const PdeQ* pq, int N, int Np, double* H) {
+  const dim3 grid((Np / 2 + 256) / 256, Np / 2 + 1);
+  if (pq)
+    hipLaunchKernelGGL(k_assemble_pairs<true>, grid, dim3(256), sizeof(cplx) * (4 * tq.m + 1) * pq->d, st, tq, *pq, N,
+                       Np, H);
+  else
+    hipLaunchKernelGGL(k_assemble_pairs<false>, grid, dim3(256), 0, st, tq, PdeQ{}, N, Np, H);
 }
 
 // Symmetric diagonal equilibration of each lambda's matrix: scl[l][r] =
@@ -344,27 +378,23 @@ static unsigned a32_tiles(int Np) {
   return nb * (nb + 1) / 2;
 }
 
-// preal[r] = p[complex mode of r]
-__global__ void k_real_weights(const double* __restrict__ p, int N, int L, double* __restrict__ preal) {
-  int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= N) return;
-  int t, k, nk;
-  real_to_complex(r, L, &t, &k, &nk);
-  preal[r] = p[k];
-}
-
-// Real right-hand sides Bre[t][r] (Np rows, zero padded) from complex b[t][k].  The real form reads
+// grid.y = 0 (with p): real-form weights preal[r] = p[complex mode of r], zero padded; grid.y = t + 1: real
+// right-hand sides Bre[t][r] (Np rows, zero padded) from complex b[t][k].  The real form reads
 // the mode k of each pair (k, -k) only (b_-k = conj b_k for real data); a NaN or Inf in either entry
 // of the pair is carried into the row, so that the residual norms report it.
-__global__ void k_rhs_real(const double* __restrict__ b, int N, int L, int Np, int ntgt,
-                           double* __restrict__ Bre) {
+__global__ void k_real_inputs(const double* __restrict__ p, const double* __restrict__ b, int N, int L, int Np,
+                              double* __restrict__ preal, double* __restrict__ Bre) {
   int r = blockIdx.x * blockDim.x + threadIdx.x;
-  int t = blockIdx.y;
   if (r >= Np) return;
+  int ty = 0, k = 0, nk = 0;
+  if (r < N) real_to_complex(r, L, &ty, &k, &nk);
+  if (blockIdx.y == 0) {
+    if (p) preal[r] = r < N ? p[k] : 0.0;
+    return;
+  }
+  const int t = blockIdx.y - 1;
   double v = 0.0;
   if (r < N) {
-    int ty, k, nk;
-    real_to_complex(r, L, &ty, &k, &nk);
     const double* bt = b + 2 * (size_t)t * N;
     const double s2 = 1.41421356237309504880;
     v = ty == 0 ? bt[2 * k] : (ty == 1 ? s2 * bt[2 * k] : -s2 * bt[2 * k + 1]);
@@ -1743,7 +1773,8 @@ __global__ __launch_bounds__(64 * TBW) void k_tri_bwd(const float* __restrict__ 
 // ------------------------------------------------------------------ FP64 residual
 // Rres[l][t] = Bre[t] - (H64 + lambda_l diag(preal)) X[l][t], for all (l, t) at once:
 // one FP64 GEMM H64 (Np x Np) times X (Np x ncolsTotal), then the diagonal and the
-// subtraction.  Column c of X/Rres is (l, t) with l = c / ntgt.
+// subtraction.  Column c of X/Rres is (l, t) with l = c / ntgt.  With R32, the scaled residual in FP32 as
+// well: the right-hand side of the next refinement step.
 // On the FP64 matrix cores (v_mfma_f64_16x16x4f64): lane l supplies A[l % 16][l / 16]
 // and B[l / 16][l % 16]; element v of lane l's accumulator is D[l / 16 + 4 v][l % 16]
 // (the FP32 form holds D[4 (l / 16) + v][l % 16] instead).  A workgroup computes 64 rows
@@ -1757,7 +1788,8 @@ __global__ __launch_bounds__(256) void k_resid64_mfma(const double* __restrict__
                                                       const double* __restrict__ X, int ncols, int ntgt,
                                                       int rhs_per_col, const double* __restrict__ Bre,
                                                       const double* __restrict__ preal,
-                                                      const double* __restrict__ lams, double* __restrict__ Rres) {
+                                                      const double* __restrict__ lams, double* __restrict__ Rres,
+                                                      const double* __restrict__ scl, float* __restrict__ R32) {
   constexpr int TM = 64, TN = 32 * WN, KC = 16;
   constexpr int PH = TM * KC / 256, PX = TN * KC / 256;
   __shared__ double Hs[2][KC][TM + 4];  // Hs[k][row]
@@ -1827,6 +1859,7 @@ __global__ __launch_bounds__(256) void k_resid64_mfma(const double* __restrict__
         const double ax = acc[i][j][v] + (r < N ? lam * preal[r] * xv : 0.0);
         const double bv = (r < N) ? Bre[(size_t)(rhs_per_col ? c : t) * Np + r] : 0.0;
         Rres[(size_t)c * Np + r] = bv - ax;
+        if (R32) R32[(size_t)c * Np + r] = (float)((bv - ax) * scl[(size_t)l * Np + r]);
       }
   }
 }
@@ -1844,7 +1877,8 @@ __global__ __launch_bounds__(512) void k_resid64_rows(const double* __restrict__
                                                       const double* __restrict__ X, int ncols, int ntgt,
                                                       int rhs_per_col, const double* __restrict__ Bre,
                                                       const double* __restrict__ preal,
-                                                      const double* __restrict__ lams, double* __restrict__ Rres) {
+                                                      const double* __restrict__ lams, double* __restrict__ Rres,
+                                                      const double* __restrict__ scl, float* __restrict__ R32) {
   __shared__ double part[8][16][16 * NCT + 1];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
   const int r0 = blockIdx.x * 16, c0 = blockIdx.y * 16 * NCT;
@@ -1882,16 +1916,18 @@ __global__ __launch_bounds__(512) void k_resid64_rows(const double* __restrict__
     const double ax = a + (r < N ? lams[l] * preal[r] * xv : 0.0);
     const double bv = (r < N) ? Bre[(size_t)(rhs_per_col ? c : t) * Np + r] : 0.0;
     Rres[(size_t)c * Np + r] = bv - ax;
+    if (R32) R32[(size_t)c * Np + r] = (float)((bv - ax) * scl[(size_t)l * Np + r]);
   }
 }
 
 static void launch_resid(hipStream_t st, const double* H, int N, int Np, const double* X, int ncols, int ntgt,
-                         int rhs_per_col, const double* Bre, const double* preal, const double* lams, double* R) {
+                         int rhs_per_col, const double* Bre, const double* preal, const double* lams, double* R,
+                         const double* scl, float* R32) {
   if (ncols <= kRowsCols) {
     const int nct = (ncols + 15) / 16;
 #define FK_ROWS(NCT)                                                                                                \
   hipLaunchKernelGGL(k_resid64_rows<NCT>, dim3(Np / 16, (nct + NCT - 1) / NCT), dim3(512), 0, st, H, N, Np, X,       \
-                     ncols, ntgt, rhs_per_col, Bre, preal, lams, R)
+                     ncols, ntgt, rhs_per_col, Bre, preal, lams, R, scl, R32)
     if (nct == 1) FK_ROWS(1);
     else if (nct == 2) FK_ROWS(2);
     else if (nct == 3) FK_ROWS(3);
@@ -1917,55 +1953,63 @@ static void launch_resid(hipStream_t st, const double* H, int N, int Np, const d
   const dim3 grid(Np / 64, (ncols + TN - 1) / TN);
   if (best_wn == 4)
     hipLaunchKernelGGL(k_resid64_mfma<4>, grid, dim3(256), 0, st, H, N, Np, X, ncols, ntgt, rhs_per_col, Bre, preal,
-                       lams, R);
+                       lams, R, scl, R32);
   else if (best_wn == 3)
     hipLaunchKernelGGL(k_resid64_mfma<3>, grid, dim3(256), 0, st, H, N, Np, X, ncols, ntgt, rhs_per_col, Bre, preal,
-                       lams, R);
+                       lams, R, scl, R32);
   else
     hipLaunchKernelGGL(k_resid64_mfma<2>, grid, dim3(256), 0, st, H, N, Np, X, ncols, ntgt, rhs_per_col, Bre, preal,
-                       lams, R);
+                       lams, R, scl, R32);
 }
 
-// Column norms squared of Rres and of the right-hand sides (per column), FP64.
-__global__ __launch_bounds__(256) void k_colnorm2(const double* __restrict__ V, int Np, double* __restrict__ out) {
-  __shared__ double part[256];
+// Sum over a workgroup of 256 threads, in thread 0.
+__device__ __forceinline__ double sum256(double s, double* part) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+  __syncthreads();
+  return (part[0] + part[1]) + (part[2] + part[3]);
+}
+
+// Column norms squared (one workgroup per column), FP64; the context's error flags behind them (as
+// doubles at out[flag_at ..]), so that one copy brings both.
+__global__ __launch_bounds__(256) void k_colnorm2(const double* __restrict__ V, int Np, double* __restrict__ out,
+                                                  const int* __restrict__ flags, int flag_at) {
+  __shared__ double part[4];
   const double* v = V + (size_t)blockIdx.x * Np;
   double s = 0.0;
-  for (int i = threadIdx.x; i < Np; i += blockDim.x) s += v[i] * v[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[blockIdx.x] = part[0];
+  for (int i = threadIdx.x; i < Np; i += 256) s += v[i] * v[i];
+  s = sum256(s, part);
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
+  if (blockIdx.x == 0 && threadIdx.x < kFlagCount) out[flag_at + threadIdx.x] = (double)flags[threadIdx.x];
 }
 
-// b = (float)(S a) and x += S d, with the per-lambda scaling; element i is
-// (lambda, target, row) = (i / (ntgt Np), ., i % Np).
-__global__ void k_scale_d2f(const double* __restrict__ a, const double* __restrict__ scl, int Np, int ntgt,
-                            float* __restrict__ b, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int64_t l = i / ((int64_t)ntgt * Np);
-  int r = (int)(i % Np);
-  b[i] = (float)(a[i] * scl[l * Np + r]);
+// Start of a solve: R32 = S rhs in FP32 for every column (l, t) = (c / ntgt, c % ntgt), from per-target (or
+// per-column) right-hand sides, and the norms squared of the right-hand sides.
+__global__ __launch_bounds__(256) void k_refine_init(const double* __restrict__ rhs, int per_col,
+                                                     const double* __restrict__ scl, int Np, int ntgt,
+                                                     float* __restrict__ R32, double* __restrict__ norms) {
+  __shared__ double part[4];
+  const int c = blockIdx.x, l = c / ntgt;
+  const double* v = rhs + (size_t)(per_col ? c : c - l * ntgt) * Np;
+  double s = 0.0;
+  for (int i = threadIdx.x; i < Np; i += 256) {
+    const double x = v[i];
+    R32[(size_t)c * Np + i] = (float)(x * scl[(size_t)l * Np + i]);
+    s += x * x;
+  }
+  s = sum256(s, part);
+  if (threadIdx.x == 0) norms[c] = s;
 }
+
+// X = (first ? 0 : X) + S d, with the per-lambda scaling; column blockIdx.y = (lambda, target).
 __global__ void k_scale_axpy_f2d(const float* __restrict__ a, const double* __restrict__ scl, int Np, int ntgt,
-                                 double* __restrict__ b, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int64_t l = i / ((int64_t)ntgt * Np);
-  int r = (int)(i % Np);
-  b[i] += scl[l * Np + r] * (double)a[i];
-}
-__global__ void k_rep_rhs(const double* __restrict__ Bre, int Np, int ntgt, int nlam, double* __restrict__ R) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t tot = (int64_t)nlam * ntgt * Np;
-  if (i >= tot) return;
-  int64_t c = i / Np;
-  int t = (int)(c % ntgt);
-  R[i] = Bre[(size_t)t * Np + (i - c * Np)];
+                                 double* __restrict__ X, int first) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= Np) return;
+  const size_t i = (size_t)blockIdx.y * Np + r;
+  const double v = scl[(size_t)(blockIdx.y / ntgt) * Np + r] * (double)a[i];
+  X[i] = first ? v : X[i] + v;
 }
 
 }  // namespace fk
@@ -1988,7 +2032,8 @@ SolveLayout solve_layout(int N, int nlam, int ntgt, void* base, size_t cap) {
   s.A32 = cv.take<float>((size_t)nlam * Np * Np);
   s.Linv = cv.take<float>((size_t)nlam * Np * NB);
   s.preal = cv.take<double>(Np);
-  s.lams = cv.take<double>(nlam);
+  s.lams = cv.take<double>((size_t)nlam + N);   // and, behind them, the complex-mode weights: one upload
+  s.pcx = s.lams ? s.lams + nlam : nullptr;
   s.Bre = cv.take<double>((size_t)ntgt * Np);
   s.X64 = cv.take<double>(nc * Np);
   s.R64 = cv.take<double>(nc * Np);
@@ -2001,7 +2046,6 @@ SolveLayout solve_layout(int N, int nlam, int ntgt, void* base, size_t cap) {
   s.norms = cv.take<double>(2 * nc + nlam + 64);
   s.Hv = cv.take<double>(Np * Np);
   s.Bv = cv.take<double>((size_t)ntgt * Np);
-  s.pcx = cv.take<double>((size_t)N);
   s.scl = cv.take<double>((size_t)nlam * Np);
   s.dsym = cv.take<double>((size_t)2 * N);
   // parts of the split paired updates: 768 tiles of 64 x 128 at most (fewer for small systems)
@@ -2203,52 +2247,45 @@ static fk_status trsm_all(fk_ctx* ctx, const SolveLayout& s, const DenseShape& s
 // With check_flags, every step's norm read-back also brings the context's error flags (the stages
 // queued before the solve raised them: input NaN, range, not positive definite), and those are
 // reported first: the caller then needs no synchronization of its own before the solve.
+// after(): what the caller does with X, queued behind every step whose norms are checked, ahead of the
+// host's wait for them (and queued again should a further step follow).
+template <class After>
 static fk_status refine_solve(fk_ctx* ctx, const SolveLayout& s, const DenseShape& sh, const double* rhs_cols,
-                              double* X, int* iters_out, double* resid_out, int* bad_out,
-                              bool check_flags = false) {
-  const int64_t tot = (int64_t)s.nlam * s.ntgt * s.Np;
+                              double* X, int* iters_out, double* resid_out, int* bad_out, bool check_flags,
+                              After after) {
   const int nc = s.nlam * s.ntgt;
-  const int thr = 256;
-  const int blocks = (int)((tot + thr - 1) / thr);
-  // R64 = rhs
-  if (rhs_cols) {
-    FK_HIP(hipMemcpyAsync(s.R64, rhs_cols, sizeof(double) * tot, hipMemcpyDeviceToDevice, ctx->stream));
-  } else {
-    hipLaunchKernelGGL(k_rep_rhs, dim3(blocks), dim3(thr), 0, ctx->stream, s.Bre, s.Np, s.ntgt, s.nlam, s.R64);
-  }
-  FK_HIP(hipMemsetAsync(X, 0, sizeof(double) * tot, ctx->stream));
-  // norms of the right-hand sides
-  hipLaunchKernelGGL(k_colnorm2, dim3(nc), dim3(256), 0, ctx->stream, s.R64, s.Np, s.norms + nc);
+  const double* rhs = rhs_cols ? rhs_cols : s.Bre;
+  const int per_col = rhs_cols ? 1 : 0;
+  hipLaunchKernelGGL(k_refine_init, dim3(nc), dim3(256), 0, ctx->stream, rhs, per_col, s.scl, s.Np, s.ntgt, s.R32,
+                     s.norms + nc);
   const int maxit = ctx->opt.max_refine;
   const double tol = ctx->opt.refine_tol;
-  // the norms come back through the context's pinned staging area (an asynchronous copy)
-  double* nh = static_cast<double*>(stage_take(ctx, sizeof(double) * 2 * nc));
+  // the norms and flags come back through the context's pinned staging area (an asynchronous copy)
+  const size_t back = (size_t)2 * nc + kFlagCount;
+  double* nh = static_cast<double*>(stage_take(ctx, sizeof(double) * back));
   if (!nh) return FK_EHIP;
   int it = 0;
   double worst = 0.0;
   int bad = -1;
   for (;; ++it) {
-    hipLaunchKernelGGL(k_scale_d2f, dim3(blocks), dim3(thr), 0, ctx->stream, s.R64, s.scl, s.Np, s.ntgt, s.R32,
-                       tot);
     fk_status st = trsm_all(ctx, s, sh, s.R32, s.Y32, s.D32);
     if (st != FK_OK) return st;
-    hipLaunchKernelGGL(k_scale_axpy_f2d, dim3(blocks), dim3(thr), 0, ctx->stream, s.D32, s.scl, s.Np, s.ntgt, X,
-                       tot);
-    // R64 = rhs - A X
-    launch_resid(ctx->stream, s.H64, s.N, s.Np, X, nc, s.ntgt, rhs_cols ? 1 : 0, rhs_cols ? rhs_cols : s.Bre,
-                 s.preal, s.lams, s.R64);
+    hipLaunchKernelGGL(k_scale_axpy_f2d, dim3((s.Np + 255) / 256, nc), dim3(256), 0, ctx->stream, s.D32, s.scl, s.Np,
+                       s.ntgt, X, it == 0);
+    // R64 = rhs - A X, and S R64 for the next step
+    launch_resid(ctx->stream, s.H64, s.N, s.Np, X, nc, s.ntgt, per_col, rhs, s.preal, s.lams, s.R64, s.scl, s.R32);
     FK_HIP(hipGetLastError());
     // Below 1e-8 the FP32-class first solve never meets the tolerance on its own: its check (a host
     // wait) is skipped and the first refinement step queued behind it; errors it would have found
     // (NaN, flags) are found by the next check with the same status.
     if (it == 0 && maxit > 0 && tol < 1e-8) continue;
-    hipLaunchKernelGGL(k_colnorm2, dim3(nc), dim3(256), 0, ctx->stream, s.R64, s.Np, s.norms);
-    FK_HIP(hipMemcpyAsync(nh, s.norms, sizeof(double) * 2 * nc, hipMemcpyDeviceToHost, ctx->stream));
-    if (check_flags)
-      FK_HIP(hipMemcpyAsync(ctx->flags_host, ctx->flags, sizeof(int) * kFlagCount, hipMemcpyDeviceToHost,
-                            ctx->stream));
+    hipLaunchKernelGGL(k_colnorm2, dim3(nc), dim3(256), 0, ctx->stream, s.R64, s.Np, s.norms, ctx->flags, 2 * nc);
+    FK_HIP(hipMemcpyAsync(nh, s.norms, sizeof(double) * back, hipMemcpyDeviceToHost, ctx->stream));
+    st = after();
+    if (st != FK_OK) return st;
     FK_HIP(hipStreamSynchronize(ctx->stream));
     if (check_flags) {
+      for (int i = 0; i < kFlagCount; ++i) ctx->flags_host[i] = (int)nh[2 * nc + i];
       const fk_status fs = flag_status(ctx);
       if (fs != FK_OK) {
         *iters_out = it;
@@ -2375,34 +2412,33 @@ fk_status solve_impl(fk_ctx* ctx, const SolveProblem& P, const SolveLayout& s, d
   const int L = P.L;
   hipEvent_t* ev = ctx->ev;
   FK_HIP(hipEventRecord(ev[5], ctx->stream));
-  // penalty weights (complex modes) -> device, real-form weights
-  fk_status up = stage_upload(ctx, s.pcx, P.p.data(), sizeof(double) * N);
-  if (up == FK_OK) up = stage_upload(ctx, s.lams, P.lams.data(), sizeof(double) * s.nlam);
-  if (up != FK_OK) return up;
-  FK_HIP(hipMemsetAsync(s.preal, 0, sizeof(double) * Np, ctx->stream));
-  hipLaunchKernelGGL(k_real_weights, dim3((N + 255) / 256), dim3(256), 0, ctx->stream, s.pcx, N, L, s.preal);
+  // lambdas and penalty weights (complex modes) -> device, real-form weights and right-hand sides
+  {
+    double* h = static_cast<double*>(stage_take(ctx, sizeof(double) * ((size_t)s.nlam + N)));
+    if (!h) return FK_EHIP;
+    std::memcpy(h, P.lams.data(), sizeof(double) * s.nlam);
+    std::memcpy(h + s.nlam, P.p.data(), sizeof(double) * N);
+    FK_HIP(hipMemcpyAsync(s.lams, h, sizeof(double) * ((size_t)s.nlam + N), hipMemcpyHostToDevice, ctx->stream));
+  }
+  hipLaunchKernelGGL(k_real_inputs, dim3((Np + 255) / 256, s.ntgt + 1), dim3(256), 0, ctx->stream, s.pcx, P.b, N, L, Np,
+                     s.preal, s.Bre);
   // FP64 real-form Gram (+ dense lambda-independent penalty)
-  const int64_t tot2 = (int64_t)Np * Np;
-  const int gb = (int)((tot2 + 255) / 256);
   if (P.kind == SolveProblem::kToeplitz) {
-    ToeplitzQ q{P.M, P.m, P.d};
-    hipLaunchKernelGGL(k_assemble_real<ToeplitzQ>, dim3(gb), dim3(256), 0, ctx->stream, q, N, L, Np, s.H64);
+    launch_assemble_pairs(ctx->stream, ToeplitzQ{P.M, P.m, P.d}, nullptr, N, Np, s.H64);
   } else if (P.kind == SolveProblem::kToeplitzPde) {
-    up = stage_upload(ctx, s.dsym, P.dsym.data(), sizeof(double) * 2 * N);
+    const fk_status up = stage_upload(ctx, s.dsym, P.dsym.data(), sizeof(double) * 2 * N);
     if (up != FK_OK) return up;
-    using PQ = SumQ<ToeplitzQ, PdeQ>;
-    PQ q{ToeplitzQ{P.M, P.m, P.d}, PdeQ{s.dsym, P.m, P.d, P.mu, P.lo[0], P.hi[0], P.lo[1], P.hi[1]}};
-    hipLaunchKernelGGL(k_assemble_real<PQ>, dim3(gb), dim3(256), 0, ctx->stream, q, N, L, Np, s.H64);
+    const PdeQ pq{s.dsym, P.m, P.d, P.mu, P.lo[0], P.hi[0], P.lo[1], P.hi[1]};
+    launch_assemble_pairs(ctx->stream, ToeplitzQ{P.M, P.m, P.d}, &pq, N, Np, s.H64);
   } else {
-    DenseQ q{P.B, N};
-    hipLaunchKernelGGL(k_assemble_real<DenseQ>, dim3(gb), dim3(256), 0, ctx->stream, q, N, L, Np, s.H64);
+    const int64_t tot2 = (int64_t)Np * Np;
+    hipLaunchKernelGGL(k_assemble_real<DenseQ>, dim3((unsigned)((tot2 + 255) / 256)), dim3(256), 0, ctx->stream,
+                       DenseQ{P.B, N}, N, L, Np, s.H64);
   }
   hipLaunchKernelGGL(k_make_scale, dim3((Np + 255) / 256, s.nlam), dim3(256), 0, ctx->stream, s.H64, s.preal,
                      s.lams, N, Np, s.scl);
   hipLaunchKernelGGL(k_make_a32, dim3(a32_tiles(Np)), dim3(256), 0, ctx->stream, s.H64, s.preal, s.lams, s.scl, N, Np,
                      s.nlam, s.A32);
-  hipLaunchKernelGGL(k_rhs_real, dim3((Np + 255) / 256, s.ntgt), dim3(256), 0, ctx->stream, P.b, N, L, Np,
-                     s.ntgt, s.Bre);
   FK_HIP(hipGetLastError());
   DenseShape sh;
   bool factored = false;
@@ -2421,12 +2457,15 @@ fk_status solve_impl(fk_ctx* ctx, const SolveProblem& P, const SolveLayout& s, d
   // the flags of the earlier stages and of the factorization come back with the first residual norms
   int iters = 0, bad = -1;
   double resid = 0.0;
-  st = refine_solve(ctx, s, sh, nullptr, s.X64, &iters, &resid, &bad, true);
-  hipLaunchKernelGGL(k_theta_from_real, dim3((N + 255) / 256, s.nlam * s.ntgt), dim3(256), 0, ctx->stream, s.X64,
-                     N, L, Np, s.ntgt, theta_out);
-  FK_HIP(hipGetLastError());
-  FK_HIP(hipEventRecord(ev[8], ctx->stream));
-  FK_HIP(hipEventSynchronize(ev[8]));
+  auto write_theta = [&]() -> fk_status {
+    hipLaunchKernelGGL(k_theta_from_real, dim3((N + 255) / 256, s.nlam * s.ntgt), dim3(256), 0, ctx->stream, s.X64,
+                       N, L, Np, s.ntgt, theta_out);
+    FK_HIP(hipGetLastError());
+    FK_HIP(hipEventRecord(ev[8], ctx->stream));
+    return FK_OK;
+  };
+  st = refine_solve(ctx, s, sh, nullptr, s.X64, &iters, &resid, &bad, true, write_theta);
+  if (st == FK_EHIP) return st;
   if (info) {
     info->refine_iters = iters;
     info->resid_rel = resid;
@@ -2479,17 +2518,15 @@ __global__ void k_negate(double* __restrict__ v, int64_t n) {
 fk_status heldout_mse_impl(fk_ctx* ctx, const SolveLayout& s, int d, int m, const double* Mv, const double* bv,
                            const double* yv2, double* mse) {
   const int N = s.N, Np = s.Np, L = N;   // one real-form block of all N modes
-  const int64_t tot2 = (int64_t)Np * Np;
-  const int gb = (int)((tot2 + 255) / 256);
-  ToeplitzQ q{Mv, m, d};
-  hipLaunchKernelGGL(k_assemble_real<ToeplitzQ>, dim3(gb), dim3(256), 0, ctx->stream, q, N, L, Np, s.Hv);
-  hipLaunchKernelGGL(k_rhs_real, dim3((Np + 255) / 256, s.ntgt), dim3(256), 0, ctx->stream, bv, N, L, Np, s.ntgt,
-                     s.Bv);
+  launch_assemble_pairs(ctx->stream, ToeplitzQ{Mv, m, d}, nullptr, N, Np, s.Hv);
+  hipLaunchKernelGGL(k_real_inputs, dim3((Np + 255) / 256, s.ntgt + 1), dim3(256), 0, ctx->stream, nullptr, bv, N, L, Np,
+                     nullptr, s.Bv);
   const int nc = s.nlam * s.ntgt;
   // zero "lambda" for the validation product: reuse norms scratch as a zero lambda array
   FK_HIP(hipMemsetAsync(s.norms, 0, sizeof(double) * (2 * nc + s.nlam + 64), ctx->stream));
   // R = Bv - Hv X   (lambda = 0 via a zero lambda array of length nlam in norms[2nc..])
-  launch_resid(ctx->stream, s.Hv, N, Np, s.X64, nc, s.ntgt, 0, s.Bv, s.preal, s.norms + 2 * nc, s.G64);
+  launch_resid(ctx->stream, s.Hv, N, Np, s.X64, nc, s.ntgt, 0, s.Bv, s.preal, s.norms + 2 * nc, s.G64,
+               nullptr, nullptr);
   const int64_t tot = (int64_t)nc * Np;
   hipLaunchKernelGGL(k_negate, dim3((tot + 255) / 256), dim3(256), 0, ctx->stream, s.G64, tot);
   // xGx = x.(Hv x) = x.(g + bv) ; bx = bv.x
@@ -2601,7 +2638,8 @@ fk_status backward_impl(fk_ctx* ctx, const SolveLayout& s, int d, const double* 
   // u = A^-1 (gm g + gin) for every (lambda, target)
   hipLaunchKernelGGL(k_adjoint_rhs, dim3((Np + 255) / 256, nc), dim3(256), 0, ctx->stream, s.G64, gm, gin, N, L, Np,
                      s.Gadj);
-  fk_status st = refine_solve(ctx, s, dense_shape(ctx, s), s.Gadj, s.U64, &iters, &resid, &bad);
+  fk_status st = refine_solve(ctx, s, dense_shape(ctx, s), s.Gadj, s.U64, &iters, &resid, &bad, false,
+                              []() -> fk_status { return FK_OK; });
   if (st != FK_OK && st != FK_ENOCONV) return st;
   hipLaunchKernelGGL(k_grad_loglam, dim3(s.nlam), dim3(1024), 0, ctx->stream, s.U64, s.X64, s.preal, s.lams, Np,
                      s.ntgt, grad_loglam);

@@ -209,6 +209,7 @@ struct fk_ctx {
   hipStream_t stream = nullptr;
   fk_options opt{};
   int* flags = nullptr;           // device, fk::kFlagCount ints
+  bool flags_clean = false;       // the device flags hold their initial values
   int* flags_host = nullptr;      // pinned host mirror (kFlagCount ints), then kFlagCount words for counters
   hipEvent_t ev[16] = {};
   // cached deconvolution tables keyed by (K, eps bits)
@@ -239,7 +240,7 @@ void* stage_take(fk_ctx* ctx, size_t bytes);
 // Upload of a small host array through the staging area (asynchronous on the context's stream).
 fk_status stage_upload(fk_ctx* ctx, void* dst, const void* src, size_t bytes);
 // the status the host mirror of the flags holds (after a read-back that the caller synchronized)
-fk_status flag_status(const fk_ctx* ctx);
+fk_status flag_status(fk_ctx* ctx);
 
 // Type-1 stage.  Computes c_c[q] = sum_j w_cj exp(-i q.x_j) for |q_a| <= K on C
 // channels (channel 0 has weight 1 when `ones_channel`), written as complex128

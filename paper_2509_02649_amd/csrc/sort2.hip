@@ -847,14 +847,16 @@ struct Sort2Geom {
   int nblk2;            // its workgroups: every row's last slice may be short
 };
 
-// First pass: up to blk workgroups of at least 2048 points (65536, the earlier minimum, left 1e7 points to
-// 152 of the 256 CUs and 30011 to one workgroup: 97 and 98 us for the scatter against 61 and 10).  Second
-// pass: slices of slice_pts points, smaller ones where n would not give 512 of them.
+// First pass: blk workgroups of 65536 points or more; fewer points each, down to 2048, where those would not
+// fill the 256 CUs (workgroups of 65536 left 1e7 points to 152 CUs and 30011 to one: 97 and 98 us for the
+// scatter against 61 and 10).  Second pass: slices of slice_pts points, smaller ones, down to 8192, where n
+// would not give 256 of them.
 Sort2Geom sort2_geom(int64_t n, int nbx, int blk, int64_t slice_pts) {
   Sort2Geom g;
-  g.nblk1 = (int)std::min<int64_t>(blk, std::max<int64_t>(1, (n + 2047) / 2048));
+  const int64_t want = (n + 65535) / 65536;
+  g.nblk1 = (int)std::min<int64_t>(blk, want >= 256 ? want : std::max<int64_t>(1, (n + 2047) / 2048));
   g.chunk1 = (n + g.nblk1 - 1) / g.nblk1;
-  g.slice_pts = (uint32_t)std::max<int64_t>(4096, std::min<int64_t>(slice_pts, n / 512));
+  g.slice_pts = (uint32_t)std::max<int64_t>(8192, std::min<int64_t>(slice_pts, n / 256));
   g.nblk2 = (int)(nbx + n / g.slice_pts);
   return g;
 }
