@@ -16,10 +16,14 @@
 // One wave transforms one line in LDS (FP64, radix 4 with a radix-2 level when log2 Lf is
 // odd; the twiddle table is computed once per call and copied to LDS by each workgroup).
 //
+// The solver takes these passes for d = 3 and for d = 2 outside 8 <= m <= 32; the other sizes run in one kernel
+// (cg_fused.hip).
+//
 // CG.  All nlam x ntgt systems iterate together, one workgroup per system for the vector
 // updates; a system leaves the iteration (its lines and updates are skipped) once its
 // recursive residual meets the tolerance.
 #include "fk_internal.h"
+#include "cg_fft.h"
 
 #include <algorithm>
 #include <cmath>
@@ -49,83 +53,6 @@ struct LinePass {
   double spec_scale;
 };
 
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
-__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
-
-// Decimation in frequency, natural order in, bit-reversed order out, e^{-2 pi i / L}; tw[k] =
-// e^{-2 pi i k / L}, k < L / 2.  Two radix-2 levels per LDS round trip (lengths len and len / 2
-// over the four points pos, pos + len/4, pos + len/2, pos + 3 len/4 of a block), then a last
-// radix-2 level when log2 L is odd.
-__device__ __forceinline__ void dif_forward(double2* B, const double2* tw, int L, int lane) {
-  int len = L, step = 1;
-  for (; len >= 4; len >>= 2, step <<= 2) {
-    const int q = len >> 2;
-    for (int t = lane; t < L / 4; t += 64) {
-      const int grp = t / q, pos = t - grp * q;
-      const int i0 = grp * len + pos, i1 = i0 + q, i2 = i1 + q, i3 = i2 + q;
-      const double2 a0 = B[i0], a1 = B[i1], a2 = B[i2], a3 = B[i3];
-      const double2 b0 = cadd(a0, a2), b2 = cmul(csub(a0, a2), tw[pos * step]);
-      const double2 b1 = cadd(a1, a3), b3 = cmul(csub(a1, a3), tw[(pos + q) * step]);
-      const double2 w = tw[pos * step * 2];
-      B[i0] = cadd(b0, b1);
-      B[i1] = cmul(csub(b0, b1), w);
-      B[i2] = cadd(b2, b3);
-      B[i3] = cmul(csub(b2, b3), w);
-    }
-    __syncthreads();
-  }
-  if (len == 2) {
-    for (int t = lane; t < L / 2; t += 64) {
-      const double2 u = B[2 * t], v = B[2 * t + 1];
-      B[2 * t] = cadd(u, v);
-      B[2 * t + 1] = csub(u, v);
-    }
-    __syncthreads();
-  }
-}
-
-// Decimation in time, bit-reversed order in, natural order out, e^{+2 pi i / L} (unnormalised
-// inverse): a first radix-2 level when log2 L is odd, then two levels per LDS round trip
-// (lengths len and 2 len over the points pos, pos + len/2, pos + len, pos + 3 len/2).
-__device__ __forceinline__ void dit_inverse(double2* B, const double2* tw, int L, int lane) {
-  int len = 2, step = L / 2;
-  int lg = 0;
-  while ((1 << lg) < L) ++lg;
-  if (lg & 1) {
-    for (int t = lane; t < L / 2; t += 64) {
-      const double2 u = B[2 * t], v = B[2 * t + 1];
-      B[2 * t] = cadd(u, v);
-      B[2 * t + 1] = csub(u, v);
-    }
-    __syncthreads();
-    len = 4;
-    step = L / 4;
-  }
-  for (; len <= L / 2; len <<= 2, step >>= 2) {
-    const int h = len >> 1;
-    for (int t = lane; t < L / 4; t += 64) {
-      const int grp = t / h, pos = t - grp * h;
-      const int i0 = grp * 2 * len + pos, i1 = i0 + h, i2 = i0 + len, i3 = i2 + h;
-      const double2 w = cconj(tw[pos * step]);
-      const double2 c1 = cmul(B[i1], w), c3 = cmul(B[i3], w);
-      const double2 a0 = B[i0], a2 = B[i2];
-      const double2 b0 = cadd(a0, c1), b1 = csub(a0, c1), b2 = cadd(a2, c3), b3 = csub(a2, c3);
-      const double2 v2 = cmul(b2, cconj(tw[pos * (step >> 1)]));
-      const double2 v3 = cmul(b3, cconj(tw[(pos + h) * (step >> 1)]));
-      B[i0] = cadd(b0, v2);
-      B[i2] = csub(b0, v2);
-      B[i1] = cadd(b1, v3);
-      B[i3] = csub(b1, v3);
-    }
-    __syncthreads();
-  }
-}
-
 // Dynamic LDS: FLINES lines of L entries, then the L / 2 twiddles (copied from tw_g).
 __global__ __launch_bounds__(FT) void k_line_fft(LinePass a, int L, int64_t nlines, const int* __restrict__ active,
                                                  const double2* __restrict__ tw_g) {
@@ -147,7 +74,7 @@ __global__ __launch_bounds__(FT) void k_line_fft(LinePass a, int L, int64_t nlin
   double2* B = lds + wv * L;
   for (int t = lane; t < L; t += 64) B[t] = (live && t < a.nin) ? src[t * a.inner] : make_double2(0.0, 0.0);
   __syncthreads();
-  if (a.mode != kInverse) dif_forward(B, tw, L, lane);
+  if (a.mode != kInverse) dif_forward<64>(B, tw, L, lane);
   if (a.mode == kConvolve) {
     const double2* S = a.spec + o * L;
     for (int t = lane; t < L; t += 64) {
@@ -156,7 +83,7 @@ __global__ __launch_bounds__(FT) void k_line_fft(LinePass a, int L, int64_t nlin
     }
     __syncthreads();
   }
-  if (a.mode != kForward) dit_inverse(B, tw, L, lane);
+  if (a.mode != kForward) dit_inverse<64>(B, tw, L, lane);
   if (live)
     for (int t = lane; t < a.nout; t += 64) dst[t * a.inner] = B[t];
 }
@@ -490,6 +417,7 @@ struct ToepGeom {
   int d = 0, m = 0, n0 = 0, L = 0;
   int64_t N = 0, spec = 0, tmp = 0;   // complex elements: modes, spectrum, one intermediate
   double2* tw = nullptr;              // device twiddle table, L / 2 entries
+  bool four_step = true;              // Lf = 256 by k_line_fft256 (natural order of frequencies)
 };
 
 ToepGeom toep_geom(int d, int m) {
@@ -532,7 +460,7 @@ fk_status run_pass(hipStream_t st, const ToepGeom& g, const int64_t* E, int axis
   const int64_t nlines = lines * nsys;
   const int64_t blocks = (nlines + FLINES - 1) / FLINES;
   if (blocks > 0x7fffffff) return FK_EINVAL;
-  if (g.L == 256) {
+  if (g.L == 256 && g.four_step) {
     const int64_t b256 = (nlines + R16_LINES - 1) / R16_LINES;
     if (b256 > 0x7fffffff) return FK_EINVAL;
     const size_t lds = sizeof(double2) * ((size_t)R16_LINES * 16 * R16_ROW + 128);
@@ -621,6 +549,23 @@ fk_status toeplitz_apply_impl(fk_ctx* ctx, int d, int m, const double* M, int nv
                     t0, t1, nullptr);
 }
 
+// The spectra of M and, if given, Mr for d = 1, with the twiddle table that they were made with.
+fk_status toeplitz_spectra_1d(fk_ctx* ctx, int m, const double* M, const double* Mr, const double2* spec[2],
+                              const double2** tw, int* L, Carve& cv) {
+  ToepGeom g = toep_geom(1, m);
+  g.four_step = false;   // frequencies in bit-reversed order for every Lf
+  g.tw = cv.take<double2>((size_t)g.L / 2);
+  double2* sp[2] = {cv.take<double2>((size_t)g.spec), Mr ? cv.take<double2>((size_t)g.spec) : nullptr};
+  if (!cv.ok()) return FK_ENOMEM;
+  fk_status s = build_spectrum(ctx->stream, g, M, sp[0]);
+  if (s == FK_OK && Mr) s = build_spectrum(ctx->stream, g, Mr, sp[1]);
+  spec[0] = sp[0];
+  spec[1] = sp[1];
+  *tw = g.tw;
+  *L = g.L;
+  return s;
+}
+
 size_t cg_workspace(int d, int m, int nsys, int nlam, bool colloc) {
   const ToepGeom g = toep_geom(d, m);
   Carve cv(nullptr, 0);
@@ -658,6 +603,9 @@ fk_status cg_solve_impl(fk_ctx* ctx, int d, int m, const double* M, int ntgt, co
                         const std::vector<double>& lams, const std::vector<double>& pw, double mu, const double* Mr,
                         const double* Dsym, double tol, int maxit, double* theta_out, int* iters_out,
                         double* relres_out, Carve& cv) {
+  if (cg_fused_ok(d, m))
+    return cg_fused_impl(ctx, d, m, M, ntgt, b, lams, pw, mu, Mr, Dsym, tol, maxit, theta_out, iters_out, relres_out,
+                         cv);
   ToepGeom g = toep_geom(d, m);
   const int nlam = (int)lams.size();
   const int nsys = nlam * ntgt;

@@ -263,4 +263,12 @@ fk_status cg_solve_impl(fk_ctx* ctx, int d, int m, const double* M, int ntgt, co
                         const std::vector<double>& lams, const std::vector<double>& pw, double mu, const double* Mr,
                         const double* Dsym, double tol, int maxit, double* theta_out, int* iters_out,
                         double* relres_out, Carve& cv);
+// the same with one workgroup per system (cg_fused.hip), for the sizes of cg_fused_ok
+bool cg_fused_ok(int d, int m);
+fk_status cg_fused_impl(fk_ctx* ctx, int d, int m, const double* M, int ntgt, const double* b,
+                        const std::vector<double>& lams, const std::vector<double>& pw, double mu, const double* Mr,
+                        const double* Dsym, double tol, int maxit, double* theta_out, int* iters_out,
+                        double* relres_out, Carve& cv);
+fk_status toeplitz_spectra_1d(fk_ctx* ctx, int m, const double* M, const double* Mr, const double2* spec[2],
+                              const double2** tw, int* L, Carve& cv);
 }  // namespace fk
