@@ -17,8 +17,8 @@
 // Bound by LDS and FP64 issue in turn (44 and 40 % of the cycles; waves of a phase run it together): at m = 32
 // one product is 388 transforms of 128 points.  256 systems of 4225 unknowns, up to 36 iterations: 5143 -> 1233 us
 // (before: three passes of Lf = 256 per product, 113 x 36 us, and the vector updates, 36 x 26 us, all through
-// device memory).  One system of 2401 unknowns with the collocation term, 48 iterations: 2784 -> 2287 us (before:
-// 420 launches of 2 to 15 us).
+// device memory).  One system of 2401 unknowns with the collocation term, 48 iterations: 2784 -> 2287 us here (before:
+// 420 launches of 2 to 15 us), and 1358 us in four launches per iteration (below).
 // Ten waves at Lf = 128: 65 columns need nine, and the registers allow 640 threads without much spilling (1024:
 // 1399 against 1320 us).  Keeping the vectors in the columns' registers spilled (3040 us); in row order per
 // column, the updates were longer than the product.
@@ -278,11 +278,34 @@ __global__ __launch_bounds__(256) void k_spec2(const double2* __restrict__ M, in
 
 // ------------------------------------------------------------------ products
 
+// One line of axis 1 in place: transform, spectrum row `row`, inverse; x: 8 L bytes of LDS of the line.
+template <int P>
+__device__ __forceinline__ void conv_regs(double2* v, const double2* tw, double2* x, const Spec2<P>& s, int row, int l,
+                                          bool alias) {
+  const double2 x0 = v[0], x1 = v[P / 2];   // lane 0, 4m = L: positions 0 and 2m
+  const double2* S = s.S + (size_t)row * Spec2<P>::L;
+  double2 sv[P];
+  const RowExchange ex{reinterpret_cast<double*>(x)};
+  line_dft<P, false, true>(v, tw, l, ex, [&] {   // the spectrum's latency behind the second stage
+#pragma unroll
+    for (int r = 0; r < P; ++r) sv[r] = S[l + 8 * r];
+    __builtin_amdgcn_sched_barrier(0);
+  });
+#pragma unroll
+  for (int r = 0; r < P; ++r) v[r] = cmul(v[r], sv[r]);
+  line_dft<P, true, false>(v, tw, l, ex);
+  if (alias && l == 0) {
+    const double2 ep = s.edge()[2 * row], em = s.edge()[2 * row + 1];
+    v[P / 2] = cadd(v[P / 2], cmul(ep, x0));
+    v[0] = cadd(v[0], cmul(em, x1));
+  }
+}
+
 // vec[k] <- (Sigma vec)[k], k < N, in LDS; every thread of the workgroup calls apply(), after a barrier, and the
 // result is there for all when it returns.
 template <int P_>
 struct Product2 {
-  static constexpr int P = P_, L = 8 * P, NT = P == 16 ? 640 : 512, RS = L / 2 + 4;
+  static constexpr int P = P_, kLines = P, L = 8 * P, NT = P == 16 ? 640 : 512, RS = L / 2 + 4;
   static constexpr int E = ((L / 2 + 1) * (L / 2 + 1) + NT - 1) / NT;   // elements per thread of a vector
   static constexpr size_t lds_elems = (size_t)L * RS + L + 4 * RS;
   Spec2<P> sp[2];
@@ -311,23 +334,7 @@ struct Product2 {
 #pragma unroll
     for (int r = 0; r < P; ++r)
       v[r] = r <= P / 2 && l + 8 * r < n0() ? in[l + 8 * r] : make_double2(0.0, 0.0);
-    const double2 x0 = v[0], x1 = v[P / 2];   // lane 0, 4m = L: positions 0 and 2m
-    const double2* S = s.S + (size_t)row * L;
-    double2 sv[P];
-    const RowExchange ex{reinterpret_cast<double*>(x)};
-    line_dft<P, false, true>(v, tw, l, ex, [&] {   // the spectrum's latency behind the second stage
-#pragma unroll
-      for (int r = 0; r < P; ++r) sv[r] = S[l + 8 * r];
-      __builtin_amdgcn_sched_barrier(0);
-    });
-#pragma unroll
-    for (int r = 0; r < P; ++r) v[r] = cmul(v[r], sv[r]);
-    line_dft<P, true, false>(v, tw, l, ex);
-    if (alias && l == 0) {
-      const double2 ep = s.edge()[2 * row], em = s.edge()[2 * row + 1];
-      v[P / 2] = cadd(v[P / 2], cmul(ep, x0));
-      v[0] = cadd(v[0], cmul(em, x1));
-    }
+    conv_regs<P>(v, tw, x, s, row, l, alias);
 #pragma unroll
     for (int r = 0; r <= P / 2; ++r)
       if (l + 8 * r < n0()) out[l + 8 * r] = v[r];
@@ -394,7 +401,7 @@ struct Product2 {
 
 // d = 1: the line in LDS, all 256 threads on it; the spectrum is that of the passes (bit-reversed order).
 struct Product1 {
-  static constexpr int NT = 256, E = 2;
+  static constexpr int NT = 256, E = 2, kLines = 0;
   const double2* spec[2];
   const double2* tw_g;
   int m, L;
@@ -651,6 +658,329 @@ __global__ __launch_bounds__(Prod::NT) void k_cg_fused(Prod prod, CgArgs a) {
   }
 }
 
+// ------------------------------------------------------------------ few systems: an iteration in four launches
+
+// With the collocation term (two products per iteration) and Lf = 128, one workgroup per system takes 48 us (m = 24)
+// to 59 us (m = 32) per iteration.  For few systems a wave takes 8 lines of one system and one product instead,
+// and an iteration is four launches, between which the intermediate and the partial sums go through memory:
+// columns forward (with the new direction), rows, columns inverse (with the dot product), vector updates.  Every
+// workgroup that needs a sum adds the same partial sums in the same order.  Bound by latency: the four kernels
+// take 5.9, 5.3, 5.9 and 3.4 us, and a launch costs the host 6 us.
+// One system, m = 24, 48 iterations: 2287 us in one workgroup -> 1358 us.
+struct CgSplit {
+  CgArgs a;
+  int m, n0, N, it, resid;         // it: this iteration; resid: the product of theta, for the true residual
+  double2 *T[2], *p2[2], *vy;      // [nsys][L][n0] per product, directions by parity, [nsys][2][2][n0]
+  double *part1, *part2, *rho2;    // [nsys][kParts], 2 x [nsys][kParts], rho by parity [2][nsys]
+  double* dinv;                    // [nsys][N], 1 / diagonal
+  double2* tw;                     // the twiddles
+  int nsys, nc, nd;                // workgroups of the column and of the update launches
+};
+constexpr int kParts = 64, SP = 16, SL = 8 * SP;
+
+__device__ __forceinline__ void load_twiddles(double2* tw, const double2* g, int nt) {
+  for (int i = threadIdx.x; i < SL; i += nt) tw[i] = g[i];
+}
+
+// sum over the wave, the same bits in every lane
+__device__ __forceinline__ double wave_sum(double x) {
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+__device__ __forceinline__ double parts_sum(const double* p, int n) {
+  const int lane = threadIdx.x & 63;
+  return wave_sum(lane < n ? p[lane] : 0.0);
+}
+__global__ __launch_bounds__(1024) void k_split_init(CgSplit c) {
+  __shared__ double red[2 * 16];
+  const CgArgs& a = c.a;
+  const int s = blockIdx.x, N = c.N;
+  const double m0 = a.M[a.centre].x, m0r = a.Mr[a.centre].x;
+  if (s == 0 && threadIdx.x == 0) {
+    a.m0[0] = m0;
+    a.m0[1] = m0r;
+  }
+  if (s == 0) fill_twiddles<SP>(c.tw, 1024);
+  const bool ok = m0 > 0.0 && !isinf(m0) && m0r > 0.0 && !isinf(m0r);
+  const double lam = a.lams[s / a.ntgt];
+  double rz = 0.0, b2 = 0.0;
+  for (int k = threadIdx.x; ok && k < N; k += 1024) {
+    const double2 x = a.b[(int64_t)(s % a.ntgt) * N + k];
+    double dg = m0 + lam * a.pw[k];
+    dg += a.mu * m0r * (a.D[k].x * a.D[k].x + a.D[k].y * a.D[k].y);
+    const double inv = 1.0 / dg, n2 = x.x * x.x + x.y * x.y;
+    const int64_t e = (int64_t)s * N + k;
+    c.dinv[e] = inv;
+    a.theta[e] = make_double2(0.0, 0.0);
+    a.r[e] = x;
+    c.p2[0][e] = make_double2(x.x * inv, x.y * inv);
+    b2 += n2;
+    rz += n2 * inv;
+  }
+  block_sum2<1024>(rz, b2, red);
+  if (threadIdx.x == 0) {
+    c.rho2[s] = rz;
+    a.bb[s] = b2;
+    a.iters[s] = 0;
+    a.active[s] = ok && b2 > 0.0 && !isinf(b2);
+    if (ok && (!(b2 == b2) || isinf(b2))) atomicOr(&a.flags[kFlagNaN], 1);   // a NaN or Inf right-hand side
+  }
+}
+
+// Columns of one product, 8 per wave: stop test of the last iteration, p = r / dg + beta p, axis 0 forward.
+__global__ __launch_bounds__(64) void k_split_fwd(CgSplit c) {
+  constexpr int P = SP, L = SL, RS = 12;
+  __shared__ __align__(16) double2 tw[L], xch[L * RS];
+  const CgArgs& a = c.a;
+  const int s = blockIdx.y, h = blockIdx.x % 2, blk = blockIdx.x / 2;
+  const int l = threadIdx.x & 7, line = threadIdx.x >> 3, i = blk * 8 + line, N = c.N;
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0, live = i < c.n0;
+  const int64_t o = (int64_t)s * N;
+  const double2* src = (c.resid ? a.theta : c.it > 0 ? c.p2[(c.it - 1) & 1] : c.p2[0]) + o;
+  // everything is read before the sums are waited for (what a lane does not need: entry 0)
+  const bool step = !c.resid && c.it > 0;
+  load_twiddles(tw, c.tw, 64);
+  double2 v[P], y[P / 2 + 1], d[P / 2 + 1];
+  double inv[P / 2 + 1];
+#pragma unroll
+  for (int r = 0; r <= P / 2; ++r) {
+    const int k = live && l + 8 * r < c.n0 ? (l + 8 * r) * c.n0 + i : 0;
+    v[r] = src[k];
+    y[r] = a.r[o + k];
+    inv[r] = c.dinv[o + k];
+    d[r] = a.D[k];
+  }
+  double beta = 0.0;
+  if (!c.resid) {
+    const int on = a.active[s];
+    if (c.it > 0) {
+      const double rr = parts_sum(c.part2 + 2 * s * kParts, c.nd), rz = parts_sum(c.part2 + (2 * s + 1) * kParts, c.nd);
+      const double rho = c.rho2[((c.it - 1) & 1) * c.nsys + s], bb = a.bb[s];
+      if (!on) return;
+      if (first) a.iters[s] = c.it;
+      if (rr <= a.tol2 * bb) {   // seen alike, or as active = 0, by every workgroup of the system
+        if (first) a.active[s] = 0;
+        return;
+      }
+      beta = rz / rho;
+      if (first) c.rho2[(c.it & 1) * c.nsys + s] = rz;
+    }
+    if (!on) return;
+  }
+  __syncthreads();
+  if (!live) return;
+  double2* dst = c.p2[c.it & 1] + o;
+#pragma unroll
+  for (int r = 0; r < P; ++r) {
+    if (r > P / 2 || l + 8 * r >= c.n0) {
+      v[r] = make_double2(0.0, 0.0);
+      continue;
+    }
+    if (step) {
+      v[r] = make_double2(y[r].x * inv[r] + beta * v[r].x, y[r].y * inv[r] + beta * v[r].y);
+      if (h == 0) dst[(l + 8 * r) * c.n0 + i] = v[r];
+    }
+    if (h) v[r] = cmul(d[r], v[r]);
+  }
+  line_dft<P, false, true>(v, tw, l, ColExchange<RS>{xch + line});
+  double2* T = c.T[h] + (int64_t)s * L * c.n0 + i;
+#pragma unroll
+  for (int r = 0; r < P; ++r) T[(l + 8 * r) * c.n0] = v[r];
+}
+
+// Rows of one product, 8 per wave, in place; the two end rows (4m = L) from the direction.
+__global__ __launch_bounds__(64) void k_split_rows(CgSplit c, Spec2<SP> s0, Spec2<SP> s1) {
+  constexpr int P = SP, L = SL;
+  __shared__ __align__(16) double2 tw[L], xch[8 * (L / 2 + 4)];
+  const CgArgs& a = c.a;
+  const int s = blockIdx.y, h = blockIdx.x % 2, blk = blockIdx.x / 2;
+  const int l = threadIdx.x & 7, line = threadIdx.x >> 3, row = blk * 8 + line, n0 = c.n0;
+  load_twiddles(tw, c.tw, 64);
+  if (!c.resid && !a.active[s]) return;
+  __syncthreads();
+  const bool alias = 4 * c.m == L;
+  if (row >= (alias ? L + 2 : L)) return;
+  double2* T = c.T[h] + ((int64_t)s * L + row) * n0;
+  const int k0 = row == L ? 0 : 2 * c.m * n0;   // end rows: the first row of x for lag +2m, the last for -2m
+  const double2* p = (c.resid ? a.theta : c.p2[c.it & 1]) + (int64_t)s * c.N + k0;
+  double2 v[P];
+#pragma unroll
+  for (int r = 0; r < P; ++r) {
+    const int t = l + 8 * r;
+    v[r] = make_double2(0.0, 0.0);
+    if (r <= P / 2 && t < n0) v[r] = row < L ? T[t] : h ? cmul(a.D[k0 + t], p[t]) : p[t];
+  }
+  conv_regs<P>(v, tw, xch + line * (L / 2 + 4), h ? s1 : s0, row, l, alias);
+  double2* out = row < L ? T : c.vy + ((int64_t)(s * 2 + h) * 2 + row - L) * n0;
+#pragma unroll
+  for (int r = 0; r <= P / 2; ++r)
+    if (l + 8 * r < n0) out[l + 8 * r] = v[r];
+}
+
+// Columns, 8 per workgroup and a wave per product: axis 0 inverse, q = all terms (into the first N entries of
+// T[0], whose columns the wave has read), and the partial <p, q> or ||b - q||^2.
+__global__ __launch_bounds__(128) void k_split_inv(CgSplit c) {
+  constexpr int P = SP, L = SL, RS = 12;
+  __shared__ __align__(16) double2 tw[L], xch[2][L * RS];
+  const CgArgs& a = c.a;
+  const int s = blockIdx.y, h = threadIdx.x >> 6, l = threadIdx.x & 7, line = (threadIdx.x >> 3) & 7;
+  const int i = blockIdx.x * 8 + line, n0 = c.n0, N = c.N;
+  const bool live = i < n0, alias = 4 * c.m == L;
+  const int64_t o = (int64_t)s * N;
+  const double2* T = c.T[h] + (int64_t)s * L * n0 + (live ? i : 0);
+  const double2* p = (c.resid ? a.theta : c.p2[c.it & 1]) + o;
+  load_twiddles(tw, c.tw, 128);
+  // read before the transform (what a lane does not need: entry 0)
+  double2 v[P], x[P / 2 + 1], d[P / 2 + 1];
+  double lp[P / 2 + 1];
+#pragma unroll
+  for (int r = 0; r < P; ++r) v[r] = T[(l + 8 * r) * n0];
+#pragma unroll
+  for (int r = 0; r <= P / 2; ++r) {
+    const int k = live && l + 8 * r < n0 ? (l + 8 * r) * n0 + i : 0;
+    x[r] = p[k];
+    lp[r] = a.pw[k];
+    d[r] = a.D[k];
+  }
+  if (!c.resid && !a.active[s]) return;
+  __syncthreads();
+  if (live) {
+    line_dft<P, true, false>(v, tw, l, ColExchange<RS>{xch[h] + line});
+    if (alias && l == 0) {
+      const double2* vy = c.vy + (int64_t)(s * 2 + h) * 2 * n0 + i;
+      v[P / 2] = cadd(v[P / 2], vy[0]);
+      v[0] = cadd(v[0], vy[n0]);
+    }
+  }
+  if (live && h == 1) {
+#pragma unroll
+    for (int r = 0; r <= P / 2; ++r) xch[1][(l + 8 * r) * 8 + line] = v[r];
+  }
+  __syncthreads();
+  if (h == 1) return;
+  double sum = 0.0;
+  const double lam = a.lams[s / a.ntgt];
+  double2* q = c.T[0] + (int64_t)s * L * n0;
+#pragma unroll
+  for (int r = 0; r <= P / 2; ++r)
+    if (live && l + 8 * r < n0) {
+      const int k = (l + 8 * r) * n0 + i;
+      double2 y = make_double2(v[r].x + lam * lp[r] * x[r].x, v[r].y + lam * lp[r] * x[r].y);
+      const double2 w = xch[1][(l + 8 * r) * 8 + line];
+      y.x += a.mu * (d[r].x * w.x + d[r].y * w.y);
+      y.y += a.mu * (d[r].x * w.y - d[r].y * w.x);
+      if (c.resid) {
+        const double2 b = a.b[(int64_t)(s % a.ntgt) * N + k];
+        sum += (b.x - y.x) * (b.x - y.x) + (b.y - y.y) * (b.y - y.y);
+      } else {
+        q[k] = y;
+        sum += x[r].x * y.x + x[r].y * y.y;
+      }
+    }
+  sum = wave_sum(sum);
+  if (threadIdx.x == 0) c.part1[s * kParts + blockIdx.x] = sum;
+}
+
+// theta += alpha p, r -= alpha q and the partial ||r||^2 and <r, r / dg>.
+__global__ __launch_bounds__(256) void k_split_update(CgSplit c) {
+  __shared__ double red[2 * 4];
+  const CgArgs& a = c.a;
+  const int s = blockIdx.y, k = blockIdx.x * 256 + threadIdx.x, N = c.N;
+  const int kc = min(k, N - 1);
+  const int64_t e = (int64_t)s * N + kc;
+  const double2 p = c.p2[c.it & 1][e], q = c.T[0][(int64_t)s * SL * c.n0 + kc];
+  double2 t = a.theta[e], r = a.r[e];
+  const double inv = c.dinv[e], rho = c.rho2[(c.it & 1) * c.nsys + s];
+  const double pq = parts_sum(c.part1 + s * kParts, c.nc);
+  if (!a.active[s]) return;
+  if (!(pq > 0.0)) {   // seen alike, or as active = 0, by every workgroup of the system
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      a.active[s] = 0;
+      atomicOr(&a.flags[pq == pq ? kFlagNotPD : kFlagNaN], 1);
+    }
+    return;
+  }
+  const double alpha = rho / pq;
+  double rr = 0.0, rz = 0.0;
+  if (k < N) {
+    t.x += alpha * p.x;
+    t.y += alpha * p.y;
+    r.x -= alpha * q.x;
+    r.y -= alpha * q.y;
+    a.theta[e] = t;
+    a.r[e] = r;
+    rr = r.x * r.x + r.y * r.y;
+    rz = rr * inv;
+  }
+  block_sum2<256>(rr, rz, red);
+  if (threadIdx.x == 0) {
+    c.part2[2 * s * kParts + blockIdx.x] = rr;
+    c.part2[(2 * s + 1) * kParts + blockIdx.x] = rz;
+  }
+}
+
+// After the last launch: the stop test of the last iteration, and the true residual.
+__global__ __launch_bounds__(64) void k_split_end(CgSplit c) {
+  const CgArgs& a = c.a;
+  const int s = blockIdx.x;
+  const double rr = parts_sum(c.part2 + 2 * s * kParts, c.nd), e = parts_sum(c.part1 + s * kParts, c.nc);
+  if (threadIdx.x) return;
+  if (a.active[s] && c.it > 0) {
+    a.iters[s] = c.it;
+    if (rr <= a.tol2 * a.bb[s]) a.active[s] = 0;
+  }
+  a.relres[s] = a.bb[s] > 0.0 ? sqrt(e / a.bb[s]) : 0.0;
+}
+
+fk_status run_split(fk_ctx* ctx, CgSplit c, const Spec2<SP>* sp, int maxit, double* back, size_t back_bytes,
+                    int* iters_out, double* relres_out) {
+  constexpr int kCheck = 8;   // iterations between reads of the active systems
+  hipStream_t st = ctx->stream;
+  const int nsys = c.nsys;
+  char* h = static_cast<char*>(stage_take(ctx, back_bytes));
+  if (!h) return FK_EHIP;
+  const double* hm0 = reinterpret_cast<const double*>(h);
+  const int* hit = reinterpret_cast<const int*>(hm0 + 2 + nsys);
+  const int* hact = hit + nsys;
+  const dim3 cols((unsigned)(2 * c.nc), (unsigned)nsys), rows((unsigned)(2 * (4 * c.m == SL ? SP + 1 : SP)), (unsigned)nsys);
+  auto product = [&] {
+    hipLaunchKernelGGL(k_split_fwd, cols, dim3(64), 0, st, c);
+    hipLaunchKernelGGL(k_split_rows, rows, dim3(64), 0, st, c, sp[0], sp[1]);
+    hipLaunchKernelGGL(k_split_inv, dim3(c.nc, nsys), dim3(128), 0, st, c);
+  };
+  hipLaunchKernelGGL(k_split_init, dim3(nsys), dim3(1024), 0, st, c);
+  int nact = 1, done = 0;
+  while (nact > 0 && done < maxit) {
+    for (const int to = std::min(maxit, done + kCheck); done < to; ++done) {
+      c.it = done;
+      product();
+      hipLaunchKernelGGL(k_split_update, dim3(c.nd, nsys), dim3(256), 0, st, c);
+    }
+    FK_HIP(hipMemcpyAsync(h, back, back_bytes, hipMemcpyDeviceToHost, st));
+    FK_HIP(hipStreamSynchronize(st));
+    for (int i = 0; i < 2; ++i)
+      if (!(hm0[i] > 0.0) || std::isinf(hm0[i])) return FK_EINVAL;
+    nact = 0;
+    for (int i = 0; i < nsys; ++i) nact += hact[i];
+  }
+  c.it = done;
+  c.resid = 1;
+  product();
+  hipLaunchKernelGGL(k_split_end, dim3(nsys), dim3(64), 0, st, c);
+  FK_HIP(hipMemcpyAsync(h, back, back_bytes, hipMemcpyDeviceToHost, st));
+  const fk_status fs = read_flags(ctx);
+  if (fs == FK_EHIP) return fs;
+  nact = 0;
+  int mx = 0;
+  for (int i = 0; i < nsys; ++i) {
+    nact += hact[i];
+    mx = std::max(mx, hit[i]);
+  }
+  if (relres_out) std::copy(hm0 + 2, hm0 + 2 + nsys, relres_out);
+  if (iters_out) *iters_out = mx;
+  return fs == FK_OK && nact > 0 ? FK_ENOCONV : fs;
+}
+
 template <class Prod>
 fk_status run_cg(fk_ctx* ctx, const Prod& prod, CgArgs a, size_t lds, int nsys, int maxit, bool colloc, double* back,
                  size_t back_bytes, int* iters_out, double* relres_out) {
@@ -707,6 +1037,12 @@ struct CgInput {
 };
 
 // The workspace is that of the passes, which has room for their two intermediates where this needs a few KB.
+// Four launches per iteration with the collocation term and Lf = 128 up to this many systems (per solve, m = 24 and
+// 32: 1450 and 1632 against 2293 and 3069 us with 4 systems, 2041 and 2547 against 2318 and 3088 with 64).  At
+// Lf = 64 (15 us per iteration in one workgroup), and without the term (26 to 32 us), the four launches, 25 us and
+// more, gain little or lose.
+constexpr int kSplitSystems = 64;
+
 template <class Prod>
 fk_status solve_fused(fk_ctx* ctx, const CgInput& in, const Prod& prod, size_t lds, Carve& cv) {
   const int nlam = (int)in.lams.size(), nsys = nlam * in.ntgt;
@@ -743,6 +1079,31 @@ fk_status solve_fused(fk_ctx* ctx, const CgInput& in, const Prod& prod, size_t l
   h.insert(h.end(), in.pw.begin(), in.pw.begin() + in.N);
   const fk_status s = stage_upload(ctx, up, h.data(), sizeof(double) * h.size());
   if (s != FK_OK) return s;
+  if constexpr (Prod::kLines == SP) {
+    if (colloc && nsys <= kSplitSystems) {
+      const size_t n0 = 2 * (size_t)in.m + 1, t = (size_t)nsys * SL * n0;
+      CgSplit c{};
+      c.a = a;
+      c.m = in.m;
+      c.n0 = (int)n0;
+      c.N = in.N;
+      c.nsys = nsys;
+      c.nc = (int)(n0 + 7) / 8;
+      c.nd = (in.N + 255) / 256;   // at most 17 (kParts)
+      c.p2[0] = a.p;
+      c.p2[1] = a.q;
+      c.T[0] = cv.take<double2>(t);
+      c.T[1] = cv.take<double2>(t);
+      c.vy = cv.take<double2>((size_t)nsys * 4 * n0);
+      c.part1 = cv.take<double>((size_t)nsys * kParts);
+      c.part2 = cv.take<double>((size_t)nsys * 2 * kParts);
+      c.rho2 = cv.take<double>((size_t)nsys * 2);
+      c.dinv = cv.take<double>((size_t)nsys * in.N);
+      c.tw = cv.take<double2>(SL);
+      if (!cv.ok()) return FK_ENOMEM;
+      return run_split(ctx, c, prod.sp, in.maxit, back, back_bytes, in.iters_out, in.relres_out);
+    }
+  }
   return run_cg(ctx, prod, a, lds, nsys, in.maxit, colloc, back, back_bytes, in.iters_out, in.relres_out);
 }
 

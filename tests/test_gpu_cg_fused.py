@@ -77,6 +77,52 @@ def test_several_launches(fk, d, m):
     assert np.array_equal(few, th[:3])
 
 
+# with the collocation term, 64 systems take four launches per iteration and 65 one workgroup each
+@pytest.mark.parametrize("m", [17, 32])
+def test_many_collocation_systems(fk, m):
+    mu = 1e-4
+    M, b = _case(2, m, 1, 3000, 8)
+    Mr, _ = _case(2, m, 1, 500, 9, 1.5)
+    D = oracle.pde_symbol(m, 2, [[1, 1], [0, 0]], [1.0, 0.5])
+    lams = list(10.0 ** np.linspace(-4, 0, 65))
+    kw = dict(penalty="sobolev", s=2.0, tol=TOL, maxit=3000, info=True, collocation=(mu, _dev(Mr), _dev(D)))
+    th, inf = fk.solve_cg(_dev(M), _dev(b), m, lams, **kw)
+    few, inf64 = fk.solve_cg(_dev(M), _dev(b), m, lams[:64], **kw)
+    p = oracle.sobolev_weights(m, 2, 2.0)
+    C = mu * (np.conj(D)[:, None] * oracle.system_matrix(Mr, m, 0.0, p) * D[None, :])
+    S = oracle.system_matrix(M, m, 0.0, p) + C
+    for i in (0, 40, 63):
+        for x in (th, few):
+            y = x[i, 0].cpu().numpy()
+            assert np.linalg.norm(b[0] - S @ y - lams[i] * p * y) <= 2 * TOL * np.linalg.norm(b[0])
+    assert max(r[0] for r in inf["relres"]) <= 2 * TOL and max(r[0] for r in inf64["relres"]) <= 2 * TOL
+    assert abs(inf["iters"] - inf64["iters"]) <= 1
+
+
+def test_stops_with_collocation(fk):
+    m = 20
+    M, b = _case(2, m, 1, 3000, 3)
+    Mr, _ = _case(2, m, 1, 500, 9, 1.5)
+    col = (1e-4, _dev(Mr), _dev(oracle.pde_symbol(m, 2, [[1, 0], [0, 0]], [1.0, 0.5])))
+    for bad in (np.nan, np.inf):
+        c = b.copy()
+        c[0, 7] = bad
+        with pytest.raises(fk.FkError):
+            fk.solve_cg(_dev(M), _dev(c), m, [1e-3], collocation=col)
+    neg = Mr.copy()
+    neg[2 * m, 2 * m] = -1.0                    # the diagonal of Sigma_r
+    with pytest.raises(fk.FkError):
+        fk.solve_cg(_dev(M), _dev(b), m, [1e-3], collocation=(1e-4, _dev(neg), col[2]))
+    ind = np.zeros_like(M)
+    ind[2 * m, 2 * m], ind[2 * m, 2 * m + 1], ind[2 * m, 2 * m - 1] = 1.0, 4.0, 4.0
+    with pytest.raises(fk.FkError):
+        fk.solve_cg(_dev(ind), _dev(b), m, [1e-6], collocation=(1e-12, col[1], col[2]))
+    with pytest.raises(fk.FkError):             # iteration limit
+        fk.solve_cg(_dev(M), _dev(b), m, [1e-5], maxit=9, tol=1e-12, collocation=col)
+    th, inf = fk.solve_cg(_dev(M), _dev(0.0 * b), m, [1e-3], info=True, collocation=col)
+    assert inf["iters"] == 0 and float(th.abs().max()) == 0.0 and inf["relres"] == [[0.0]]
+
+
 def test_stops(fk):
     M, b = _case(2, 16, 1, 3000, 3)
     for bad in (np.nan, np.inf):
