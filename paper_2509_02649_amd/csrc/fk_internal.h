@@ -185,8 +185,9 @@ int sort2_words(int nw);
 // Buffers for any shape with at most kSortBlkMax first-pass workgroups and slices of at least
 // kSortSliceMin points.
 void sort2_carve(Carve& cv, int64_t n, int nbx, int wv, Sort2Bufs* b);
-// totals: sort2_totals(nbx) words that the caller has set to zero.
-size_t sort2_totals(int nbx);
+// totals: sort2_totals(n, nbx, nw) words that the caller has set to zero.
+bool sort2_one_pass(int64_t n, int nbx, int nw);
+size_t sort2_totals(int64_t n, int nbx, int nw);
 fk_status sort2(hipStream_t st, const void* X, fk_dtype dt, int64_t n, int64_t xstride, const void* Y, int nw,
                 int nf, int fb, int W, double scale, int tshift, int nbx, const T1Shape& shape, Sort2Bufs b,
                 uint32_t* totals, uint32_t* crd, uint32_t* wts, uint64_t* start, int* flags);

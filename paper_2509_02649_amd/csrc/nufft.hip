@@ -754,7 +754,7 @@ size_t type1_workspace(int d, int64_t n, int nw, int K, double eps) {
     }
     cv.take<double>((size_t)C * nf * nf);          // FP64 grid
     if (kind != Spread2::kAtomic) {
-      cv.take<uint32_t>(sort2_totals(g.nbx));
+      cv.take<uint32_t>((size_t)g.nbx);             // the sort's totals (one-pass sort: see type1)
     } else {
       cv.take<uint32_t>((size_t)g.nb * g.nblk);
       cv.take<uint32_t>((size_t)g.nb);
@@ -993,10 +993,11 @@ fk_status type1(fk_ctx* ctx, int d, int64_t n, fk_dtype dt, const void* X, int64
     const BinGeom g2 = bin_geom(nf, C, n, kind, 2);
     if (g2.nb > gmax.nb) gmax = g2;
   }
-  // the sort's totals follow the grid, so that one fill clears both
+  // the sort's totals follow the grid, so that one fill clears both; those of a one-pass sort, nb words (nf^2 / 64),
+  // run on into rowfft, which is written after the sort
   double* grid = cv.take<double>((size_t)C * nf * nf);
   uint32_t* cnt = split ? nullptr : cv.take<uint32_t>((size_t)gmax.nb * gmax.nblk);
-  uint32_t* totals = cv.take<uint32_t>(split ? sort2_totals(gmax.nbx) : (size_t)gmax.nb);
+  uint32_t* totals = cv.take<uint32_t>(split ? (size_t)gmax.nbx : (size_t)gmax.nb);
   double* rowfft = cv.take<double>((size_t)C * nf * L * 2);
   uint64_t* start = cv.take<uint64_t>((size_t)gmax.nb + 1);
   uint32_t* rec = cv.take<uint32_t>((size_t)n * (split ? 2 : 2 + nw));
@@ -1012,7 +1013,7 @@ fk_status type1(fk_ctx* ctx, int d, int64_t n, fk_dtype dt, const void* X, int64
     if (info) info->bin = g.T;
     FK_HIP(hipEventRecord(ev[0], ctx->stream));
     size_t clear = sizeof(double) * C * nf * nf;
-    if (split) clear = (size_t)(reinterpret_cast<char*>(totals + sort2_totals(g.nbx)) - reinterpret_cast<char*>(grid));
+    if (split) clear = (size_t)(reinterpret_cast<char*>(totals + sort2_totals(n, g.nbx, nw)) - reinterpret_cast<char*>(grid));
     FK_HIP(hipMemsetAsync(grid, 0, clear, ctx->stream));
     if (split) {
       // records for the MFMA spreads: two-pass sort, coordinates and weight words

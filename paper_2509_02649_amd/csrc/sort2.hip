@@ -19,6 +19,9 @@
 // 0..7 weight channels (records of 1, 2, 4 or 8 weight words):
 //   pass 1 as above; pass 2 -> crd / wts, grouped by bin.
 //
+// With few bins (nbx^2 <= KONE) and 0..7 weight channels one counting pass over all bins does: a batch is staged as
+// above, and its runs, 8 points and more, still fill most of a 64-byte line.
+//
 // The order of points inside a bin is not specified (LDS atomics rank them).
 #include "fk_internal.h"
 #include "fk_device.h"
@@ -31,6 +34,7 @@ namespace {
 
 constexpr int BT = 1024;       // points per staged batch, one per thread
 constexpr int KMAX = 256;      // largest bucket count (nf / MB for nf <= 1024)
+constexpr int KONE = 1024;     // largest bin count of the one-pass sort (nf <= 256 with bins of 8 x 8 cells)
 
 struct Stage {
   uint32_t cur[KMAX];             // next output position of every bucket
@@ -128,13 +132,14 @@ __device__ __forceinline__ void stage_batch(Stage& sm, int nk, bool ok, int key,
 // Pass 1 counts: bucket = bin row of every valid point, one row of nbx counts per
 // workgroup (contiguous chunks of the input), and the totals rowtot (zeroed beforehand).  Each thread
 // takes CU1 points per step, their loads issued together.
+// ONE: the buckets are the nbx = ncol^2 bins.
 constexpr int CU1 = 4;
-template <typename TX>
+template <typename TX, bool ONE = false>
 __global__ __launch_bounds__(BT) void k_s2_count1(const TX* __restrict__ X, int64_t n, int64_t xstride,
                                                   double scale, uint32_t nf_fix, int fb, uint32_t wbias,
-                                                  int tshift, int nbx, int64_t chunk, uint32_t* __restrict__ cnt,
+                                                  int tshift, int nbx, int ncol, int64_t chunk, uint32_t* __restrict__ cnt,
                                                   uint32_t* __restrict__ rowtot, int* flags) {
-  __shared__ uint32_t hist[KMAX];
+  __shared__ uint32_t hist[ONE ? KONE : KMAX];
   for (int i = threadIdx.x; i < nbx; i += blockDim.x) hist[i] = 0;
   __syncthreads();
   const int64_t beg = (int64_t)blockIdx.x * chunk;
@@ -153,7 +158,10 @@ __global__ __launch_bounds__(BT) void k_s2_count1(const TX* __restrict__ X, int6
       uint32_t U1, U2;
       bool ok = to_fixed(x1[u], scale, nf_fix, &U1, flags);
       ok = to_fixed(x2[u], scale, nf_fix, &U2, flags) && ok;
-      if (ok) atomicAdd(&hist[window_bin(U1, fb, wbias, (int)(nf_fix >> fb), tshift)], 1u);
+      if (!ok) continue;
+      int key = window_bin(U1, fb, wbias, (int)(nf_fix >> fb), tshift);
+      if constexpr (ONE) key = key * ncol + window_bin(U2, fb, wbias, (int)(nf_fix >> fb), tshift);
+      atomicAdd(&hist[key], 1u);
     }
   }
   __syncthreads();
@@ -214,6 +222,37 @@ __global__ __launch_bounds__(1024) void k_s2_scan1(uint32_t* __restrict__ cnt, i
     start1[b] = base;
     if (b == nk - 1) start1[nk] = (uint64_t)base + total;
   }
+}
+
+// The same for the one-pass sort (any nk): workgroup b takes the 16 buckets
+// from 16 b, read together, and thread (g, i) the g-th part of bucket 16 b + i's column (a workgroup per bucket
+// took 21 us for 512 x 1024 counts, of whose lines it used 4 bytes each; this takes 12 us).
+__global__ __launch_bounds__(1024) void k_s2_scan_one(uint32_t* __restrict__ cnt, int nk, int nblk,
+                                                      const uint32_t* __restrict__ tot, uint64_t* __restrict__ start) {
+  __shared__ uint32_t sh[16], part[64][17];
+  const int i = threadIdx.x & 15, g = threadIdx.x >> 4, b = blockIdx.x * 16 + i;
+  const uint32_t first = block_sum(tot, blockIdx.x * 16, sh);
+  const int k0 = (int)((int64_t)nblk * g / 64), k1 = (int)((int64_t)nblk * (g + 1) / 64);
+  const bool on = b < nk;
+  uint32_t sum = 0;
+#pragma unroll 4
+  for (int k = k0; k < k1; ++k) sum += on ? cnt[(int64_t)k * nk + b] : 0u;
+  part[g][i] = sum;
+  __syncthreads();
+  uint32_t p = first;
+  for (int j = 0; j < i; ++j) p += blockIdx.x * 16 + j < nk ? tot[blockIdx.x * 16 + j] : 0u;
+  if (on && g == 0) {
+    start[b] = p;
+    if (b == nk - 1) start[nk] = (uint64_t)p + tot[b];
+  }
+  for (int j = 0; j < g; ++j) p += part[j][i];
+#pragma unroll 4
+  for (int k = k0; k < k1; ++k)
+    if (on) {
+      const uint32_t v = cnt[(int64_t)k * nk + b];
+      cnt[(int64_t)k * nk + b] = p;
+      p += v;
+    }
 }
 
 // Workgroup `blk` of the second pass: its row and its part [q0, q1) of the row's points.  A row of len
@@ -409,13 +448,16 @@ __global__ __launch_bounds__(1024) void k_s2_scan2(uint32_t* __restrict__ cnt2, 
 template <int WV>
 constexpr int narrow_ppt() { return WV <= 2 ? 4 : (WV == 4 ? 2 : 1); }
 constexpr int kPosPpt = 8;   // points per thread of the position pass (116 KB of LDS)
+// Points per thread of the one-pass sort: twice as many for the length of its runs (FP64 points: registers).
+template <typename TX, int WV>
+constexpr int one_ppt() { return WV <= 1 && sizeof(TX) == 4 ? 8 : (WV <= 2 ? 4 : (WV == 4 ? 4 : 2)); }
 
-template <int WV, int P = narrow_ppt<WV>()>
+template <int WV, int P = narrow_ppt<WV>(), int KM = KMAX>
 struct StageN {
   static constexpr int NPT = P;
-  uint32_t cur[KMAX];
-  uint32_t hist[KMAX];
-  uint32_t lofs[KMAX];
+  uint32_t cur[KM];
+  uint32_t hist[KM];
+  uint32_t lofs[KM];
   uint32_t total;
   uint16_t sbin[BT * NPT];
   uint2 scrd[BT * NPT];
@@ -453,8 +495,8 @@ __device__ __forceinline__ void scan_counts(St& sm, int nk) {
   __syncthreads();
 }
 
-template <int WV, int P>
-__device__ __forceinline__ void write_batch_n(StageN<WV, P>& sm, uint2* __restrict__ crd_out,
+template <int WV, int P, int KM>
+__device__ __forceinline__ void write_batch_n(StageN<WV, P, KM>& sm, uint2* __restrict__ crd_out,
                                               uint32_t* __restrict__ wts_out) {
   const uint32_t total = sm.total;
   for (uint32_t q = threadIdx.x; q < total; q += BT) {
@@ -470,16 +512,18 @@ __device__ __forceinline__ void write_batch_n(StageN<WV, P>& sm, uint2* __restri
   }
 }
 
-template <typename TX, int WV>
+// ONE: the buckets are the nbx = ncol^2 bins, and the records are in their final order.
+template <typename TX, int WV, bool ONE>
 __global__ __launch_bounds__(BT) void k_s2n_scatter1(const TX* __restrict__ X, int64_t n, int64_t xstride,
                                                      const TX* __restrict__ Y, int nw, double scale,
-                                                     uint32_t nf_fix, int fb, uint32_t wbias, int tshift, int nbx,
+                                                     uint32_t nf_fix, int fb, uint32_t wbias, int tshift, int nbx, int ncol,
                                                      int64_t chunk, const uint32_t* __restrict__ off,
                                                      uint2* __restrict__ crd1, uint32_t* __restrict__ wts1,
                                                      int* flags) {
-  constexpr int NPT = narrow_ppt<WV>();
+  constexpr int NPT = ONE ? one_ppt<TX, WV>() : narrow_ppt<WV>();
+  using St = StageN<WV, NPT, ONE ? KONE : KMAX>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  StageN<WV>& sm = *reinterpret_cast<StageN<WV>*>(smem_raw);
+  St& sm = *reinterpret_cast<St*>(smem_raw);
   const int tid = threadIdx.x;
   for (int b = tid; b < nbx; b += BT) {
     sm.cur[b] = off[(int64_t)blockIdx.x * nbx + b];
@@ -492,19 +536,19 @@ __global__ __launch_bounds__(BT) void k_s2n_scatter1(const TX* __restrict__ X, i
   const int nf = (int)(nf_fix >> fb);
   // next batch in flight: point base + u BT + tid of slot u (index clamped to the
   // chunk; no target row is read when nw = 0)
-  double nx1[NPT], nx2[NPT];
+  TX nx1[NPT], nx2[NPT];
   float ny[NPT][WV > 0 ? WV : 1];
 #define FK_FETCH1N(bb)                                                                     \
   _Pragma("unroll") for (int u = 0; u < NPT; ++u) {                                        \
     const int64_t jc = min((int64_t)(bb) + u * BT + tid, end - 1);                         \
-    nx1[u] = (double)X[jc];                                                                \
-    nx2[u] = (double)X[xstride + jc];                                                      \
+    nx1[u] = X[jc];                                                                        \
+    nx2[u] = X[xstride + jc];                                                              \
     _Pragma("unroll") for (int c = 0; c < WV; ++c)                                         \
       ny[u][c] = nw > 0 ? (float)Y[(int64_t)min(c, nw - 1) * n + jc] : 0.f;               \
   }
   FK_FETCH1N(beg);
   for (int64_t base = beg; base < end; base += (int64_t)BT * NPT) {
-    double x1[NPT], x2[NPT];
+    TX x1[NPT], x2[NPT];
     float w[NPT][WV > 0 ? WV : 1];
 #pragma unroll
     for (int u = 0; u < NPT; ++u) {
@@ -523,13 +567,24 @@ __global__ __launch_bounds__(BT) void k_s2n_scatter1(const TX* __restrict__ X, i
       ok[u] = false;
       U[u] = make_uint2(0u, 0u);
       if (base + u * BT + tid < end) {
-        ok[u] = to_fixed(x1[u], scale, nf_fix, &U[u].x, flags);
-        ok[u] = to_fixed(x2[u], scale, nf_fix, &U[u].y, flags) && ok[u];
+        ok[u] = to_fixed((double)x1[u], scale, nf_fix, &U[u].x, flags);
+        ok[u] = to_fixed((double)x2[u], scale, nf_fix, &U[u].y, flags) && ok[u];
       }
       key[u] = ok[u] ? window_bin(U[u].x, fb, wbias, nf, tshift) : 0;
+      if constexpr (ONE) key[u] = ok[u] ? key[u] * ncol + window_bin(U[u].y, fb, wbias, nf, tshift) : 0;
       rank[u] = ok[u] ? atomicAdd(&sm.hist[key[u]], 1u) : 0u;
     }
-    scan_counts(sm, nbx);
+    if constexpr (ONE) {
+      __shared__ uint32_t sh[16];
+      uint32_t total;
+      __syncthreads();
+      const uint32_t before = block_scan(tid < nbx ? sm.hist[tid] : 0u, sh, &total);
+      if (tid < nbx) sm.lofs[tid] = before;
+      if (tid == 0) sm.total = total;
+      __syncthreads();
+    } else {
+      scan_counts(sm, nbx);
+    }
 #pragma unroll
     for (int u = 0; u < NPT; ++u) {
       if (!ok[u]) continue;
@@ -875,7 +930,7 @@ struct SortArgs {
 template <typename TX>
 void sort2_first(const SortArgs& a, const TX* X, const Sort2Geom& g, const Sort2Bufs& b) {
   hipLaunchKernelGGL(k_s2_count1<TX>, dim3(g.nblk1), dim3(BT), 0, a.st, X, a.n, a.xstride, a.scale, a.nf_fix, a.fb,
-                     a.wbias, a.tshift, a.nbx, g.chunk1, b.cnt1, b.rowtot, a.flags);
+                     a.wbias, a.tshift, a.nbx, a.nbx, g.chunk1, b.cnt1, b.rowtot, a.flags);
   hipLaunchKernelGGL(k_s2_scan1, dim3(a.nbx), dim3(1024), 0, a.st, b.cnt1, a.nbx, g.nblk1, b.rowtot, b.start1);
 }
 
@@ -894,9 +949,20 @@ void sort2_second(const SortArgs& a, const Sort2Geom& g, const Sort2Bufs& b, uin
 template <int WV, typename TX>
 void sort2_narrow(const SortArgs& a, const TX* X, const TX* Y, const Sort2Geom& g, const Sort2Bufs& b, uint32_t* crd,
                   uint32_t* wts) {
+  if (sort2_one_pass(a.n, a.nbx, a.nw)) {
+    const int nb = a.nbx * a.nbx;
+    uint32_t* cnt = b.crd1;   // [nblk1][nb]; the first pass's records are not needed
+    hipLaunchKernelGGL((k_s2_count1<TX, true>), dim3(g.nblk1), dim3(BT), 0, a.st, X, a.n, a.xstride, a.scale, a.nf_fix,
+                       a.fb, a.wbias, a.tshift, nb, a.nbx, g.chunk1, cnt, b.rowtot, a.flags);
+    hipLaunchKernelGGL(k_s2_scan_one, dim3((nb + 15) / 16), dim3(1024), 0, a.st, cnt, nb, g.nblk1, b.rowtot, a.start);
+    hipLaunchKernelGGL((k_s2n_scatter1<TX, WV, true>), dim3(g.nblk1), dim3(BT),
+                       sizeof(StageN<WV, one_ppt<TX, WV>(), KONE>), a.st, X, a.n, a.xstride, Y, a.nw, a.scale, a.nf_fix,
+                       a.fb, a.wbias, a.tshift, nb, a.nbx, g.chunk1, cnt, reinterpret_cast<uint2*>(crd), wts, a.flags);
+    return;
+  }
   sort2_first(a, X, g, b);
-  hipLaunchKernelGGL((k_s2n_scatter1<TX, WV>), dim3(g.nblk1), dim3(BT), sizeof(StageN<WV>), a.st, X, a.n, a.xstride, Y,
-                     a.nw, a.scale, a.nf_fix, a.fb, a.wbias, a.tshift, a.nbx, g.chunk1, b.cnt1,
+  hipLaunchKernelGGL((k_s2n_scatter1<TX, WV, false>), dim3(g.nblk1), dim3(BT), sizeof(StageN<WV>), a.st, X, a.n,
+                     a.xstride, Y, a.nw, a.scale, a.nf_fix, a.fb, a.wbias, a.tshift, a.nbx, a.nbx, g.chunk1, b.cnt1,
                      reinterpret_cast<uint2*>(b.crd1), b.wts1, a.flags);
   sort2_second<WV, false, narrow_ppt<WV>()>(a, g, b, crd, wts);
 }
@@ -979,7 +1045,13 @@ int sort2_words(int nw) {
   return wv;
 }
 
-size_t sort2_totals(int nbx) { return (size_t)nbx; }
+// One counting pass over all bins instead of two over rows and columns, wherever the bins are
+// few enough for their cursors and a batch in LDS: 1024 bins, 2e7 points without targets 416 -> 168 us, 1e8 points
+// with one target 1390 -> 1017 us, 30011 points with three 36 -> 23 us (and three launches less).
+// The counts take the place of the first pass's records (2 n words, at least 1366 points for 1024 bins).
+bool sort2_one_pass(int64_t n, int nbx, int nw) { return nw <= 7 && nbx * nbx <= KONE && n >= 4096; }
+
+size_t sort2_totals(int64_t n, int nbx, int nw) { return (size_t)nbx * (sort2_one_pass(n, nbx, nw) ? nbx : 1); }
 
 void sort2_carve(Carve& cv, int64_t n, int nbx, int wv, Sort2Bufs* b) {
   // the most first-pass workgroups and second-pass slices that any shape takes
