@@ -213,21 +213,25 @@ __device__ __forceinline__ void window_start(uint32_t U, int fb, int w, int* i0,
 }
 
 // ------------------------------------------------------------------ 1-D spread (whole grid in LDS)
-// grid: gridDim.x workgroups over contiguous chunks of points.  LDS: C * nf floats.
-// Channel 0 carries weight 1 when ones != 0; channels ones..C-1 read Y rows.
+// grid: gridDim.x workgroups over contiguous chunks of points.  LDS: C nf doubles, 1 << lc copies of each side by
+// side.  Channel 0 carries weight 1 when ones != 0; channels ones..C-1 read Y rows.
+// Bound by LDS atomics: 64 lanes add into random cells, and lanes whose cells share banks (or are the same) wait
+// for each other.  A lane adds into the copy of its number, so that only lanes 1 << lc apart can meet: 2e7 points,
+// two channels of 512 cells, 285 us with one copy -> 155 with 16.
 template <int W>
-__global__ __launch_bounds__(256) void k_spread_1d(const void* __restrict__ X, fk_dtype dt, int64_t n,
-                                                   const void* __restrict__ Y, int nw, int ones,
-                                                   int nf, int fb, double scale, EsDev es,
-                                                   double* __restrict__ grid, int* flags,
-                                                   int64_t chunk) {
+__global__ __launch_bounds__(1024) void k_spread_1d(const void* __restrict__ X, fk_dtype dt, int64_t n,
+                                                    const void* __restrict__ Y, int nw, int ones,
+                                                    int nf, int fb, double scale, EsDev es,
+                                                    double* __restrict__ grid, int* flags,
+                                                    int64_t chunk, int lc) {
   extern __shared__ double lds[];
   const int C = nw + ones;
-  for (int i = threadIdx.x; i < C * nf; i += blockDim.x) lds[i] = 0.0;
+  for (int i = threadIdx.x; i < (C * nf) << lc; i += blockDim.x) lds[i] = 0.0;
   __syncthreads();
   const int64_t beg = (int64_t)blockIdx.x * chunk;
   const int64_t end = min(n, beg + chunk);
   const uint32_t nf_fix = (uint32_t)nf << fb;
+  double* copy = lds + (threadIdx.x & ((1 << lc) - 1));
   for (int64_t j = beg + threadIdx.x; j < end; j += blockDim.x) {
     uint32_t U;
     if (!to_fixed(load_coord(X, dt, j), scale, nf_fix, &U, flags)) continue;
@@ -243,24 +247,25 @@ __global__ __launch_bounds__(256) void k_spread_1d(const void* __restrict__ X, f
       for (int a = 0; a < W; ++a) {
         int l = base + a;
         l = l >= nf ? l - nf : l;
-        atomicAdd(&lds[l], (double)k[a]);
+        atomicAdd(&copy[l << lc], (double)k[a]);
       }
     }
     for (int c = 0; c < nw; ++c) {
       float wc = load_weight(Y, dt, (int64_t)c * n + j);
       if (!(wc == wc) || isinf(wc)) { atomicOr(&flags[kFlagNaN], 1); continue; }
-      double* g = lds + (c + ones) * nf;
+      double* g = copy + (((c + ones) * nf) << lc);
 #pragma unroll
       for (int a = 0; a < W; ++a) {
         int l = base + a;
         l = l >= nf ? l - nf : l;
-        atomicAdd(&g[l], (double)(wc * k[a]));
+        atomicAdd(&g[l << lc], (double)(wc * k[a]));
       }
     }
   }
   __syncthreads();
   for (int i = threadIdx.x; i < C * nf; i += blockDim.x) {
-    double v = lds[i];
+    double v = 0.0;
+    for (int q = 0; q < 1 << lc; ++q) v += lds[(i << lc) + ((q + threadIdx.x) & ((1 << lc) - 1))];
     if (v != 0.0) atomicAdd(&grid[i], v);
   }
 }
@@ -777,12 +782,27 @@ size_t type1_workspace(int d, int64_t n, int nw, int K, double eps) {
   return sz + 256;
 }
 
+// Copies of the 1-D grid in LDS: as many as 144 KB hold, with one workgroup of 1024 threads per CU, from 2^19 points on
+// (2e7 points: 72 KB and two workgroups 237 us for the whole transform, 36 KB and four 263, 144 KB 222).  Below,
+// many small workgroups have fewer cells to clear and to add up.
+constexpr int64_t kCopies1dPoints = 1 << 19;
+constexpr size_t kCopies1dBytes = 144 * 1024;
+constexpr int k1dBlocks = 256;
+
 template <int W>
-static void launch_spread_1d(fk_ctx* ctx, int blocks, size_t lds, const void* X, fk_dtype dt, int64_t n,
-                             const void* Y, int nw, int ones, int nf, int fb, double scale, EsDev es, double* grid,
-                             int64_t chunk) {
-  hipLaunchKernelGGL(k_spread_1d<W>, dim3(blocks), dim3(256), lds, ctx->stream, X, dt, n, Y, nw, ones, nf,
-                     fb, scale, es, grid, ctx->flags, chunk);
+static void launch_spread_1d(fk_ctx* ctx, const void* X, fk_dtype dt, int64_t n, const void* Y, int nw, int ones, int nf,
+                             int fb, double scale, EsDev es, double* grid) {
+  const size_t cells = (size_t)(nw + ones) * nf;
+  int blocks = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (n + 4095) / 4096)), threads = 256, lc = 0;
+  if (n >= kCopies1dPoints) {
+    while (lc < 5 && (sizeof(double) * cells << (lc + 1)) <= kCopies1dBytes) ++lc;
+    if (lc > 0) {
+      blocks = k1dBlocks;
+      threads = 1024;
+    }
+  }
+  hipLaunchKernelGGL(k_spread_1d<W>, dim3(blocks), dim3(threads), sizeof(double) * cells << lc, ctx->stream, X, dt, n, Y,
+                     nw, ones, nf, fb, scale, es, grid, ctx->flags, (n + blocks - 1) / blocks, lc);
 }
 
 template <int W>
@@ -919,8 +939,6 @@ fk_status type1(fk_ctx* ctx, int d, int64_t n, fk_dtype dt, const void* X, int64
     if (!cv.ok()) return FK_ENOMEM;
     FK_HIP(hipEventRecord(ev[0], ctx->stream));
     FK_HIP(hipMemsetAsync(grid, 0, sizeof(double) * C * nf, ctx->stream));
-    int blocks = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (n + 4095) / 4096));
-    int64_t chunk = (n + blocks - 1) / blocks;
     // channels per launch: as many whole FP64 grids as 160 KB of LDS holds (the ones channel
     // goes with the first launch); the grid is [C][nf], so a launch writes channels ones + c0 ..
     const int per = (int)((160 * 1024) / (sizeof(double) * nf));
@@ -931,9 +949,7 @@ fk_status type1(fk_ctx* ctx, int d, int64_t n, fk_dtype dt, const void* X, int64
       const int cnt = std::min(per - first, nw - c0);
       const void* Yc = Y ? static_cast<const void*>(static_cast<const char*>(Y) + esz * (size_t)c0 * n) : nullptr;
       double* gc = grid + (size_t)(first ? 0 : 1 + c0) * nf;
-      const size_t lds = sizeof(double) * (size_t)(cnt + first) * nf;
-      FK_W_SWITCH(W, launch_spread_1d<WW>(ctx, blocks, lds, X, dt, n, Yc, cnt, first, nf, fb, scale, es, gc,
-                                          chunk));
+      FK_W_SWITCH(W, launch_spread_1d<WW>(ctx, X, dt, n, Yc, cnt, first, nf, fb, scale, es, gc));
       c0 += cnt;
     }
     FK_HIP(hipGetLastError());
