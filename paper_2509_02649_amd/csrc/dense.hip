@@ -2241,6 +2241,183 @@ static fk_status trsm_all(fk_ctx* ctx, const SolveLayout& s, const DenseShape& s
   return FK_OK;
 }
 
+// ------------------------------------------------------------------ small systems: refinement in one launch
+
+// Up to 128 unknowns (one or two block columns) and 4 targets: a workgroup per lambda runs the FP32 solve with the
+// factors, the FP64 update and the FP64 residual, `steps` times, and the norms, in place of ten launches of 1.5 to
+// 3.6 us.  Bound by latency: 18 us (N = 101, one target, two steps).  Whole solves, ten launches / this: N = 41
+// 111 / 71 us, N = 101 113 / 94, with 16 lambdas and 1, 4, 16 targets 129 / 108, 135 / 122 and 139 / 163 (the
+// residual's columns, 16 at a time in registers, take longer than their own launch).
+// Wave t owns column t of the FP32 solve, so its five products need no barrier.  NT: the
+// columns of the residual's registers.
+constexpr int kSmallCols = 4;
+constexpr int CL = kSmallCols + 1;   // row stride of the right-hand sides in LDS
+constexpr size_t kSmallLds = sizeof(float) * (3 * NB * (NB + 1) + 2 * NB * CL) +
+                             sizeof(double) * (2 * NB * CL + 4 * kSmallCols + 2 * NB * 33);
+
+template <int NT>
+__global__ __launch_bounds__(256) void k_small_refine(const float* __restrict__ A, const float* __restrict__ Linv,
+                                                      const double* __restrict__ H, int N, int Np,
+                                                      const double* __restrict__ rhs, int per_col,
+                                                      const double* __restrict__ scl, const double* __restrict__ preal,
+                                                      const double* __restrict__ lams, int ntgt, int nc, int first,
+                                                      int steps, double* __restrict__ X, float* __restrict__ R32,
+                                                      double* __restrict__ norms, const int* __restrict__ flags) {
+  extern __shared__ __align__(16) double lds_small[];
+  double* Xs = lds_small;                                     // [128][CL]
+  double* part = Xs + 2 * NB * CL;                            // [4][kSmallCols]
+  double* Hc = part + 4 * kSmallCols;                         // the residual's chunk of H, [128][33]
+  float* Bs = reinterpret_cast<float*>(Hc + 2 * NB * 33);     // [128][CL]
+  float* Ls = Bs + 2 * NB * CL;                               // three blocks, rows of 65
+  const int l = blockIdx.x, nb = Np / NB, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const double* sl = scl + (size_t)l * Np;
+  // every load of the blocks and of the first chunk of H in flight together
+  float4 tile[3][4];
+#pragma unroll
+  for (int blk = 0; blk < 3; ++blk)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = 4 * (tid + 256 * u), row = e / NB, col = e % NB;
+      if (blk == 0 || nb == 2)
+        tile[blk][u] = *reinterpret_cast<const float4*>(blk == 1 ? A + (size_t)l * Np * Np + (size_t)(NB + row) * Np + col
+                                                                 : Linv + ((size_t)l * nb + blk / 2) * NB * NB + e);
+    }
+  double2 hc[8];
+  auto fetch_h = [&](int k0) {   // thread: rows tid / 16 + 16 u, two columns
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      hc[u] = *reinterpret_cast<const double2*>(H + (size_t)min(tid / 16 + 16 * u, Np - 1) * Np + k0 + 2 * (tid & 15));
+  };
+  fetch_h(0);
+#pragma unroll
+  for (int blk = 0; blk < 3; ++blk)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = 4 * (tid + 256 * u);
+      float* o = Ls + blk * NB * (NB + 1) + e / NB * (NB + 1) + e % NB;
+      const float4 v = tile[blk][u];
+      if (blk == 0 || nb == 2) {
+        o[0] = blk == 1 ? split_unpack(__float_as_uint(v.x)) : v.x;   // the panel: FP16 pairs
+        o[1] = blk == 1 ? split_unpack(__float_as_uint(v.y)) : v.y;
+        o[2] = blk == 1 ? split_unpack(__float_as_uint(v.z)) : v.z;
+        o[3] = blk == 1 ? split_unpack(__float_as_uint(v.w)) : v.w;
+      }
+    }
+  auto rhs_at = [&](int t, int r) { return rhs[(size_t)(per_col ? l * ntgt + t : t) * Np + r]; };
+  if (w < ntgt) {
+    const int t = w, c = l * ntgt + t;
+    double s = 0.0;
+    for (int r = lane; r < Np; r += 64) {
+      if (first) {
+        const double x = rhs_at(t, r);
+        Bs[r * CL + t] = (float)(x * sl[r]);
+        Xs[r * CL + t] = 0.0;
+        s += x * x;
+      } else {
+        Bs[r * CL + t] = R32[(size_t)c * Np + r];
+        Xs[r * CL + t] = X[(size_t)c * Np + r];
+      }
+    }
+    if (first) {
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+      if (lane == 0) norms[nc + c] = s;
+    }
+  }
+  // out = sum_k M[lane][k] b[k][w] (or M^T), M one of the staged blocks
+  float out;
+  auto product = [&](int blk, bool tr, int row0) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const float* m = Ls + blk * NB * (NB + 1) + (tr ? lane : lane * (NB + 1));
+    const int sm = tr ? NB + 1 : 1;
+    const float* b = Bs + row0 * CL + w;
+    out = 0.f;
+#pragma unroll 16
+    for (int k = 0; k < NB; ++k) out = fmaf(m[k * sm], b[k * CL], out);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  auto put = [&](int row0, bool sub) {
+    float* o = Bs + (row0 + lane) * CL + w;
+    *o = sub ? *o - out : out;
+  };
+  const int r = tid >> 1, h = tid & 1;   // of the residual: row, half of k
+  for (int step = 0; step < steps; ++step) {
+    __syncthreads();
+    if (w < ntgt) {
+      product(0, false, 0);   // y_0 = inv(L_00) r_0
+      put(0, false);
+      if (nb == 2) {
+        product(1, false, 0);   // y_1 = inv(L_11) (r_1 - L_10 y_0)
+        put(NB, true);
+        product(2, false, NB);
+        put(NB, false);
+        product(2, true, NB);   // x_1 = inv(L_11)^T y_1
+        put(NB, false);
+        product(1, true, NB);   // x_0 = inv(L_00)^T (y_0 - L_10^T x_1)
+        put(0, true);
+      }
+      product(0, true, 0);
+      put(0, false);
+      for (int q = lane; q < Np; q += 64) Xs[q * CL + w] += sl[q] * (double)Bs[q * CL + w];
+    }
+    __syncthreads();
+    // residual: 32 columns of H at a time
+    double acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = 0.0;
+    for (int k0 = 0; k0 < Np; k0 += 32) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        double* o = Hc + (tid / 16 + 16 * u) * 33 + 2 * (tid & 15);
+        o[0] = hc[u].x;
+        o[1] = hc[u].y;
+      }
+      __syncthreads();
+      fetch_h(k0 + 32 < Np ? k0 + 32 : 0);
+      if (r < Np) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const int k = 16 * h + q;
+          const double a = Hc[r * 33 + k];
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[t] = fma(a, Xs[(k0 + k) * CL + t], acc[t]);
+        }
+      }
+      __syncthreads();
+    }
+    const double lp = r < N ? lams[l] * preal[r] : 0.0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      double e = 0.0;
+      acc[t] += __shfl_xor(acc[t], 1, 64);
+      if (t < ntgt && r < Np) {
+        e = (r < N ? rhs_at(t, r) : 0.0) - (acc[t] + lp * Xs[r * CL + t]);
+        if (h == 0) Bs[r * CL + t] = (float)(e * sl[r]);
+      }
+      if (step == steps - 1) {
+        double q = h == 0 ? e * e : 0.0;
+        for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+        if (lane == 0) part[w * kSmallCols + t] = q;
+      }
+    }
+    __syncthreads();
+  }
+  if (w < ntgt) {
+    const int t = w, c = l * ntgt + t;
+    for (int q = lane; q < Np; q += 64) {
+      X[(size_t)c * Np + q] = Xs[q * CL + t];
+      R32[(size_t)c * Np + q] = Bs[q * CL + t];
+    }
+    if (lane == 0) norms[c] = (part[t] + part[kSmallCols + t]) + (part[2 * kSmallCols + t] + part[3 * kSmallCols + t]);
+  }
+  if (l == 0 && tid < kFlagCount) norms[2 * nc + tid] = (double)flags[tid];
+}
+
+static bool small_solve(const SolveLayout& s) { return s.Np <= 2 * NB && s.ntgt <= kSmallCols; }
+
 // Solve (H64 + lambda diag(preal)) X = RHS for all (lambda, target) with FP32
 // factors and FP64 refinement.  RHS given per target (Bre) or per column (rhs_cols).
 // Returns the number of refinement steps and the worst relative residual.
@@ -2256,8 +2433,10 @@ static fk_status refine_solve(fk_ctx* ctx, const SolveLayout& s, const DenseShap
   const int nc = s.nlam * s.ntgt;
   const double* rhs = rhs_cols ? rhs_cols : s.Bre;
   const int per_col = rhs_cols ? 1 : 0;
-  hipLaunchKernelGGL(k_refine_init, dim3(nc), dim3(256), 0, ctx->stream, rhs, per_col, s.scl, s.Np, s.ntgt, s.R32,
-                     s.norms + nc);
+  const bool small = small_solve(s);
+  if (!small)
+    hipLaunchKernelGGL(k_refine_init, dim3(nc), dim3(256), 0, ctx->stream, rhs, per_col, s.scl, s.Np, s.ntgt, s.R32,
+                       s.norms + nc);
   const int maxit = ctx->opt.max_refine;
   const double tol = ctx->opt.refine_tol;
   // the norms and flags come back through the context's pinned staging area (an asynchronous copy)
@@ -2268,18 +2447,32 @@ static fk_status refine_solve(fk_ctx* ctx, const SolveLayout& s, const DenseShap
   double worst = 0.0;
   int bad = -1;
   for (;; ++it) {
-    fk_status st = trsm_all(ctx, s, sh, s.R32, s.Y32, s.D32);
-    if (st != FK_OK) return st;
-    hipLaunchKernelGGL(k_scale_axpy_f2d, dim3((s.Np + 255) / 256, nc), dim3(256), 0, ctx->stream, s.D32, s.scl, s.Np,
-                       s.ntgt, X, it == 0);
-    // R64 = rhs - A X, and S R64 for the next step
-    launch_resid(ctx->stream, s.H64, s.N, s.Np, X, nc, s.ntgt, per_col, rhs, s.preal, s.lams, s.R64, s.scl, s.R32);
-    FK_HIP(hipGetLastError());
     // Below 1e-8 the FP32-class first solve never meets the tolerance on its own: its check (a host
     // wait) is skipped and the first refinement step queued behind it; errors it would have found
     // (NaN, flags) are found by the next check with the same status.
-    if (it == 0 && maxit > 0 && tol < 1e-8) continue;
-    hipLaunchKernelGGL(k_colnorm2, dim3(nc), dim3(256), 0, ctx->stream, s.R64, s.Np, s.norms, ctx->flags, 2 * nc);
+    const bool unchecked = it == 0 && maxit > 0 && tol < 1e-8;
+    fk_status st = FK_OK;
+    if (small) {
+      auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(s.nlam), dim3(256), kSmallLds, ctx->stream, s.A32, s.Linv, s.H64, s.N, s.Np, rhs,
+                           per_col, s.scl, s.preal, s.lams, s.ntgt, nc, it == 0, unchecked ? 2 : 1, X, s.R32, s.norms,
+                           ctx->flags);
+      };
+      if (s.ntgt == 1) run(k_small_refine<1>);
+      else run(k_small_refine<kSmallCols>);
+      FK_HIP(hipGetLastError());
+      if (unchecked) ++it;
+    } else {
+      st = trsm_all(ctx, s, sh, s.R32, s.Y32, s.D32);
+      if (st != FK_OK) return st;
+      hipLaunchKernelGGL(k_scale_axpy_f2d, dim3((s.Np + 255) / 256, nc), dim3(256), 0, ctx->stream, s.D32, s.scl, s.Np,
+                         s.ntgt, X, it == 0);
+      // R64 = rhs - A X, and S R64 for the next step
+      launch_resid(ctx->stream, s.H64, s.N, s.Np, X, nc, s.ntgt, per_col, rhs, s.preal, s.lams, s.R64, s.scl, s.R32);
+      FK_HIP(hipGetLastError());
+      if (unchecked) continue;
+      hipLaunchKernelGGL(k_colnorm2, dim3(nc), dim3(256), 0, ctx->stream, s.R64, s.Np, s.norms, ctx->flags, 2 * nc);
+    }
     FK_HIP(hipMemcpyAsync(nh, s.norms, sizeof(double) * back, hipMemcpyDeviceToHost, ctx->stream));
     st = after();
     if (st != FK_OK) return st;

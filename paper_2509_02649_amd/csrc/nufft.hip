@@ -793,7 +793,10 @@ template <int W>
 static void launch_spread_1d(fk_ctx* ctx, const void* X, fk_dtype dt, int64_t n, const void* Y, int nw, int ones, int nf,
                              int fb, double scale, EsDev es, double* grid) {
   const size_t cells = (size_t)(nw + ones) * nf;
-  int blocks = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (n + 4095) / 4096)), threads = 256, lc = 0;
+  // workgroups of 4096 points; few points in smaller ones, down to 512, over up to 256 CUs (a thread's points follow
+  // one another: 10000 points 16.7 -> 5.3 us)
+  int blocks = (int)std::min<int64_t>(1024, std::max<int64_t>((n + 4095) / 4096, std::min<int64_t>(256, (n + 511) / 512)));
+  int threads = 256, lc = 0;
   if (n >= kCopies1dPoints) {
     while (lc < 5 && (sizeof(double) * cells << (lc + 1)) <= kCopies1dBytes) ++lc;
     if (lc > 0) {
