@@ -626,16 +626,20 @@ __device__ inline double recip64(double x) {
 // for both columns.  The finished panels are FP16 pairs (split tiles in LDS, products on the
 // FP16 matrix cores); one LDS buffer per operand, the next k's tiles loaded into registers
 // while the current ones are multiplied.
+// Without PART: the panels kfirst <= k < kend, and G pairs of columns from kb on in one launch.  The workgroups of a row's
+// G pairs run side by side on one XCD, so that its panel, the bulk of the traffic, comes from memory once for all
+// (64 lambdas, N = 4225: 8.7 -> 7.9 ms of updates with G = 2).
 template <bool PART>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_left_update2(float* __restrict__ A,
-                                                                                             int Np, int kb,
-                                                                                             int nlam, int nsplit,
+                                                                                             int Np, int kb, int kfirst,
+                                                                                             int kend, int G, int nlam,
+                                                                                             int nsplit,
                                                                                              float* __restrict__ part) {
   __shared__ __align__(16) SplitTile As;
   __shared__ __align__(16) SplitTile B0;
   __shared__ __align__(16) SplitTile B1;
   const int rows = Np / NB - kb;
-  int l, i, k0 = 0, k1 = kb, sidx = 0;
+  int l, i, k0 = kfirst, k1 = kend, sidx = 0;
   if constexpr (PART) {
     // workgroup (sidx, l, i): panels k0 <= k < k1 of the split sidx of the sum
     const int b = blockIdx.x;
@@ -645,7 +649,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     k0 = (int)((int64_t)kb * sidx / nsplit);
     k1 = (int)((int64_t)kb * (sidx + 1) / nsplit);
   } else {
-    xcd_place(rows, nlam, &l, &i);
+    xcd_place(rows * G, nlam, &l, &i);
+    const int p = i % G;
+    i = i / G - 2 * p;
+    if (i < 0) return;   // above the pair's diagonal blocks
+    kb += 2 * p;
   }
   i += kb;
   float* Al = A + (size_t)l * Np * Np;
@@ -2075,6 +2083,12 @@ static int update_split(int wgs, int kb, int part_tiles) {
 // tile read once (64 lambdas, N = 4225: 11.40 ms up to 1024 workgroups, 11.20 always).
 constexpr int kFusedPanelWgs = 1024;
 
+// Pairs of block columns that one unsplit update takes: two where the lower triangles of all lambdas are past what the
+// caches hold (256 MB), and a pair's pass over the row panels comes from memory.  Whole factorization, one pair /
+// two / four: N = 4225, 64 lambdas (2.3 GB) 11.17 / 10.46 / 10.55 ms, 16 lambdas (590 MB) 3.74 / 3.68 / 3.57, 8 lambdas
+// (290 MB) 2.26 / 2.29 / 2.26; N = 2401, 16 lambdas (190 MB) 1.19 / 1.21 / 1.21; N = 1089, 64 lambdas 565 / 580 / 594 us.
+static int update_pairs(const SolveLayout& s) { return 2.0 * s.Np * s.Np * s.nlam > 4e8 ? 2 : 1; }
+
 // Factor A32[l] = L L^T for every lambda: left-looking blocked Cholesky, per block column an
 // update with the finished panels (one pass over the column), the factorization of the
 // diagonal block, the solve of the panel below it.
@@ -2113,13 +2127,25 @@ static fk_status factor_all(fk_ctx* ctx, const SolveLayout& s, const DenseShape&
       const int wgs = (nb - kb) * s.nlam;
       const int nsplit = update_split(wgs, kb, s.part_tiles);
       if (nsplit > 1) {
-        hipLaunchKernelGGL(k_left_update2<true>, dim3(wgs * nsplit), dim3(256), 0, ctx->stream, s.A32, s.Np, kb,
+        hipLaunchKernelGGL(k_left_update2<true>, dim3(wgs * nsplit), dim3(256), 0, ctx->stream, s.A32, s.Np, kb, 0, kb, 1,
                            s.nlam, nsplit, s.upart);
         hipLaunchKernelGGL(k_left_update2_sum, dim3(wgs * 8), dim3(256), 0, ctx->stream, s.A32, s.Np, kb, s.nlam,
                            nsplit, s.upart);
       } else {
-        hipLaunchKernelGGL(k_left_update2<false>, dim3(wgs), dim3(256), 0, ctx->stream, s.A32, s.Np, kb, s.nlam, 1,
-                           nullptr);
+        // G pairs at once; inside the group, a pair then takes the panels of the pairs before it
+        const int G = std::max(1, std::min(update_pairs(s), (nb - kb) / 2));
+        hipLaunchKernelGGL(k_left_update2<false>, dim3(wgs * G), dim3(256), 0, ctx->stream, s.A32, s.Np, kb, 0, kb, G,
+                           s.nlam, 1, nullptr);
+        for (int p = 0; p < G; ++p) {
+          const int c = kb + 2 * p;
+          if (p > 0)
+            hipLaunchKernelGGL(k_left_update2<false>, dim3((nb - c) * s.nlam), dim3(256), 0, ctx->stream, s.A32, s.Np, c,
+                               kb, c, 1, s.nlam, 1, nullptr);
+          finish(c, false);
+          finish(c + 1, true);
+        }
+        kb += 2 * G;
+        continue;
       }
       finish(kb, false);
       finish(kb + 1, true);
