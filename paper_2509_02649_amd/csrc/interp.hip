@@ -8,6 +8,7 @@
 // kept (a real estimator has Hermitian-symmetric theta).
 //   Re f(x) ~= sum_l Re(g_l) phi(l - u),  g_l = sum_q (-1)^q theta_q / Phihat(q h) e^{2 pi i q l / nf}.
 #include "fk_internal.h"
+#include "cg_fft.h"
 
 #include <algorithm>
 #include <cmath>
@@ -16,69 +17,72 @@
 
 namespace fk {
 
-// Inverse DFT of one line with pruned input frequencies q = -K..K:
-//   out[l] = sum_q in[q + K] * f(q) * e^{+2 pi i q l / nf},
-// f(q) = (-1)^q / phihat[|q|] when phihat != nullptr, else 1.
-// Input elements (complex) at in + line_in + (q+K)*istride; output complex (or
-// real part only, when oreal) at out + line_out + l*ostride.
-__global__ __launch_bounds__(256) void k_ifft_line(const double* __restrict__ in, int64_t istride,
-                                                   int64_t in_outer, int64_t in_inner, int lines_inner, int K,
-                                                   const double* __restrict__ phihat, int nf, int logn,
-                                                   double* __restrict__ out, int oreal, int64_t ostride,
-                                                   int64_t out_outer, int64_t out_inner) {
-  __shared__ double re[1024], im[1024];
-  const int line = blockIdx.x;
-  const int lo = line / lines_inner, li = line - lo * lines_inner;
-  const double* src = in + 2 * (lo * in_outer + li * in_inner);
-  for (int i = threadIdx.x; i < nf; i += blockDim.x) {
-    re[i] = 0.0;
-    im[i] = 0.0;
+// Inverse DFT of a line with pruned input frequencies q = -K..K:
+//   out[l] = sum_q in[q + K] * f(q) * e^{+2 pi i q l / nf},  f(q) = (-1)^q / phihat[|q|].
+// Line (lo, li), li < inner: input elements (complex) at in + lo in_outer + li in_inner + (q + K) istride, output
+// (complex; REAL: the real part in FP32) at out + lo out_outer + li out_inner + l ostride, all in elements.
+// Bound by LDS and memory: NT = nf / 4 lanes (at most 64) per line, radix 4, 256 / NT lines per workgroup, one
+// twiddle table for all.  (A workgroup per line with radix-2 levels and a sine and cosine per butterfly took 40.8 us
+// per pass for two 128^3 grids, and a FP64 grid and its conversion came after it; this takes 11 us, and
+// 30 for the last, to FP32.)
+template <int NT, bool REAL>
+__global__ __launch_bounds__(256) void k_ifft_lines(const double2* __restrict__ in, int64_t istride, int64_t in_outer,
+                                                    int64_t in_inner, int inner, int64_t nlines, int K,
+                                                    const double* __restrict__ phihat, int nf, int logn,
+                                                    void* __restrict__ out, int64_t ostride, int64_t out_outer,
+                                                    int64_t out_inner) {
+  extern __shared__ __align__(16) double2 ibuf[];
+  constexpr int LINES = 256 / NT;
+  const int tid = threadIdx.x, L = 2 * K + 1, ls = nf + 1;
+  double2* tw = ibuf + LINES * ls;
+  double* fac = reinterpret_cast<double*>(tw + nf / 2);
+  const int64_t line0 = (int64_t)blockIdx.x * LINES;
+  const int cnt = (int)min((int64_t)LINES, nlines - line0);
+  for (int k = tid; k < nf / 2; k += 256) {
+    double sn, cs;
+    sincospi(-2.0 * k / nf, &sn, &cs);
+    tw[k] = make_double2(cs, sn);
+  }
+  for (int q = tid; q <= K; q += 256) fac[q] = (q & 1) ? -1.0 / phihat[q] : 1.0 / phihat[q];
+  for (int e = tid; e < LINES * ls; e += 256) ibuf[e] = make_double2(0.0, 0.0);
+  __syncthreads();
+  for (int e = tid; e < LINES * L; e += 256) {   // along the line where it is contiguous, else across the lines
+    const int j = istride == 1 ? e / L : e % LINES, qi = istride == 1 ? e - j * L : e / LINES, q = qi - K;
+    if (j >= cnt) continue;
+    const int64_t line = line0 + j, lo = line / inner, li = line - lo * inner;
+    const double2 v = in[lo * in_outer + li * in_inner + qi * istride];
+    const double f = fac[q < 0 ? -q : q];
+    ibuf[j * ls + (__brev((unsigned)(q & (nf - 1))) >> (32 - logn))] = make_double2(v.x * f, v.y * f);
   }
   __syncthreads();
-  for (int q = -K + (int)threadIdx.x; q <= K; q += blockDim.x) {
-    int l = q < 0 ? q + nf : q;
-    int r = __brev((unsigned)l) >> (32 - logn);
-    double f = 1.0;
-    if (phihat) {
-      int aq = q < 0 ? -q : q;
-      f = 1.0 / phihat[aq];
-      if (aq & 1) f = -f;
-    }
-    re[r] = src[2 * (q + K) * istride] * f;
-    im[r] = src[2 * (q + K) * istride + 1] * f;
-  }
-  __syncthreads();
-  for (int len = 2; len <= nf; len <<= 1) {
-    const int half = len >> 1;
-    for (int t = threadIdx.x; t < nf / 2; t += blockDim.x) {
-      int grp = t / half, pos = t - grp * half;
-      int i = grp * len + pos, j = i + half;
-      double sn, cs;
-      sincospi(2.0 * pos / len, &sn, &cs);
-      double vr = re[j] * cs - im[j] * sn;
-      double vi = re[j] * sn + im[j] * cs;
-      double ur = re[i], ui = im[i];
-      re[i] = ur + vr;
-      im[i] = ui + vi;
-      re[j] = ur - vr;
-      im[j] = ui - vi;
-    }
-    __syncthreads();
-  }
-  double* dst = out + (lo * out_outer + li * out_inner) * (oreal ? 1 : 2);
-  for (int l = threadIdx.x; l < nf; l += blockDim.x) {
-    if (oreal) {
-      dst[l * ostride] = re[l];
-    } else {
-      dst[2 * l * ostride] = re[l];
-      dst[2 * l * ostride + 1] = im[l];
-    }
+  dit_inverse<NT>(ibuf + tid / NT * ls, tw, nf, tid % NT);
+  for (int e = tid; e < LINES * nf; e += 256) {
+    const int j = ostride == 1 ? e / nf : e % LINES, l = ostride == 1 ? e - j * nf : e / LINES;
+    if (j >= cnt) continue;
+    const int64_t line = line0 + j, lo = line / inner, li = line - lo * inner;
+    const int64_t o = lo * out_outer + li * out_inner + l * ostride;
+    const double2 v = ibuf[j * ls + l];
+    if constexpr (REAL) static_cast<float*>(out)[o] = (float)v.x;
+    else static_cast<double2*>(out)[o] = v;
   }
 }
 
-__global__ void k_d2f_grid(const double* __restrict__ a, float* __restrict__ b, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) b[i] = (float)a[i];
+template <bool REAL>
+static void ifft_lines(hipStream_t st, const double* in, int64_t istride, int64_t in_outer, int64_t in_inner, int inner,
+                       int64_t nlines, int K, const double* phihat, int nf, int logn, void* out, int64_t ostride,
+                       int64_t out_outer, int64_t out_inner) {
+  auto launch = [&](auto kernel, int nt) {
+    const int lines = 256 / nt;
+    const size_t lds = sizeof(double2) * ((size_t)lines * (nf + 1) + nf / 2) + sizeof(double) * (K + 1);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((nlines + lines - 1) / lines)), dim3(256), lds, st,
+                       reinterpret_cast<const double2*>(in), istride, in_outer, in_inner, inner, nlines, K, phihat, nf,
+                       logn, out, ostride, out_outer, out_inner);
+  };
+  if (nf <= 16) launch(k_ifft_lines<4, REAL>, 4);
+  else if (nf == 32) launch(k_ifft_lines<8, REAL>, 8);
+  else if (nf == 64) launch(k_ifft_lines<16, REAL>, 16);
+  else if (nf == 128) launch(k_ifft_lines<32, REAL>, 32);
+  else launch(k_ifft_lines<64, REAL>, 64);
 }
 
 // ES kernel psi(s) = exp(beta (sqrt(1 - (2s/w)^2) - 1)) with beta pre-multiplied by log2 e, so that
@@ -119,6 +123,77 @@ __device__ __forceinline__ bool window_at(double x, double scale, int w, int* i0
   *i0 = (int)c;
   *s0 = (float)(c - u);
   return true;
+}
+
+// d = 2 and 3, W <= 8, from grids in memory: a wave per point, lane b W + c at cell (b, c) of the window's last two
+// axes (d = 3: the first axis in a loop).  A load then touches W rows of the window instead of 64 unrelated cells,
+// which is what a lane per point waits for.  A wave takes ppw points in turn: a lane per point computes the window
+// and the kernel values first.  300 000 points x 2 sets, d = 3, 128^3 cells: 1107 us with a lane per point, 392 so.
+template <int W, int D>
+__global__ __launch_bounds__(256) void k_interp_wave(const float* __restrict__ grid, int nf, int T,
+                                                     const void* __restrict__ Xq, fk_dtype dt, int64_t nq, int ppw,
+                                                     EsDev2 es, float* __restrict__ out, int* flags) {
+  static_assert(W * W <= 64 && (D == 2 || D == 3), "a window's plane in one wave");
+  constexpr int RW = 2 * W + 1;
+  __shared__ float tab[4][64 * RW];   // kernel values of the last two axes, per point
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t j0 = ((int64_t)blockIdx.x * 4 + w) * ppw, j = j0 + lane;
+  if (j0 >= nq) return;
+  const bool mine = lane < ppw && j < nq;
+  auto ld = [&](int64_t idx) -> double {
+    return dt == FK_F64 ? static_cast<const double*>(Xq)[idx] : (double)static_cast<const float*>(Xq)[idx];
+  };
+  int i[3] = {0, 0, 0};
+  float s[3] = {0.f, 0.f, 0.f};
+  bool ok = mine;
+#pragma unroll
+  for (int a = 0; a < D; ++a) ok = mine && window_of(ld(a * nq + (mine ? j : j0)), nf, W, &i[a + 3 - D], &s[a + 3 - D]) && ok;
+  if (mine && !ok) atomicOr(&flags[kFlagRange], 1);
+  float k1[W];
+#pragma unroll
+  for (int a = 0; a < W; ++a) {
+    k1[a] = D == 3 ? es_eval2(s[0] + (float)a, es) : 1.f;
+    tab[w][lane * RW + a] = ok ? es_eval2(s[1] + (float)a, es) : 0.f;
+    tab[w][lane * RW + W + a] = es_eval2(s[2] + (float)a, es);
+  }
+  if (!ok) i[0] = i[1] = i[2] = 0;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const bool cell = lane < W * W;
+  const int b = cell ? lane / W : 0, c = cell ? lane - b * W : 0;
+  const int64_t plane = (int64_t)nf * nf, cells = D == 3 ? plane * nf : plane;
+  const int np = (int)min((int64_t)ppw, nq - j0);
+  for (int t = 0; t < T; ++t) {
+    const float* g = grid + t * cells;
+    float res = 0.f;
+#pragma unroll 4
+    for (int p = 0; p < np; ++p) {
+      const int p1 = __builtin_amdgcn_readlane(i[0], p), p2 = __builtin_amdgcn_readlane(i[1], p),
+                p3 = __builtin_amdgcn_readlane(i[2], p);
+      int l2 = p2 + b, l3 = p3 + c;
+      l2 = l2 < 0 ? l2 + nf : (l2 >= nf ? l2 - nf : l2);
+      l3 = l3 < 0 ? l3 + nf : (l3 >= nf ? l3 - nf : l3);
+      const float* q = g + l2 * nf + l3;
+      const float wt = cell ? tab[w][p * RW + b] * tab[w][p * RW + W + c] : 0.f;
+      float acc = 0.f;
+      if constexpr (D == 3) {
+#pragma unroll
+        for (int a = 0; a < W; ++a) {
+          int l1 = p1 + a;
+          l1 = l1 < 0 ? l1 + nf : (l1 >= nf ? l1 - nf : l1);
+          acc = fmaf(q[l1 * plane], __int_as_float(__builtin_amdgcn_readlane(__float_as_int(k1[a]), p)), acc);
+        }
+      } else {
+        acc = *q;
+      }
+      acc *= wt;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+      res = lane == p ? acc : res;
+    }
+    if (mine) out[(int64_t)t * nq + j] = ok ? res : __int_as_float(0x7fc00000);
+  }
 }
 
 template <int W>
@@ -677,15 +752,17 @@ static void launch_direct(fk_ctx* ctx, int d, dim3 grid, const double2* th, int 
 // Direct sums instead of the transform, where they are estimated to take less: per point and set 0.25 ns
 // and 0.45 (d = 3: 0.65, a sine and cosine per row) ps per mode, lanes past the last mode counted
 // (measured: 0.65, 2.1 and 8.0 ns at d = 2, m = 8, 32 and 60; 4.7 and 28 ns at d = 3, m = 6 and 16; 0.23
-// at d = 1, m = 50), against what the transform costs before its first point: three launches more, and
-// grids that grow with m (about 5 us at d = 1; 9, 13 and 25 us at d = 2, m = 8, 32 and 60; 42 and 100 us
-// at d = 3, m = 6 and 16), of which three quarters are taken.
+// at d = 1, m = 50), and a workgroup's chain of 58 ns per row, against what the transform costs before its first
+// point: launches more, and grids that grow with m (about 5 us at d = 1; 9, 13 and 25 us at d = 2, m = 8, 32 and
+// 60, of which three quarters are taken; 20 us at d = 3).  Whole calls, direct / transform: d = 3, m = 6, 2000
+// points 36 / 46 us, m = 8, 2000 points 44 / 49, 4000 points 60 / 49, m = 12 and 16, 50 points 62 / 46 and 91 / 62.  Up to 16 points (two workgroups) take the direct
+// sums at any m, for their FP64 results.
 static bool direct_ok(int d, int m, int T, int64_t nq) {
   const int L = 2 * m + 1;
   const double rows = std::pow((double)L, d - 1), lanes = 8.0 * (L <= 40 ? 5 : (L <= 72 ? 9 : 17));
   const double per_point = 0.25e-3 + rows * lanes * (d == 3 ? 0.65e-6 : 0.45e-6);   // microseconds
-  const double fixed = d == 1 ? 4.0 : (d == 2 ? 6.0 + 0.2 * m : 28.0 + 1.4e-3 * rows * L);
-  return (double)nq * T * per_point <= fixed;
+  const double fixed = d == 1 ? 4.0 : (d == 2 ? 6.0 + 0.2 * m : 20.0);
+  return (double)nq * T * per_point <= fixed && (d < 3 || nq <= 16 || 0.058 * rows <= fixed);
 }
 
 // The type-2 stage on a caller-given workspace and deconvolution table (device, plan.K + 1 doubles).
@@ -724,35 +801,49 @@ static fk_status predict_impl(fk_ctx* ctx, const EsPlan& plan, const double* phi
   double* tmp = d == 2 ? cv.take<double>((size_t)T * nf * L * 2) : nullptr;
   double* ta = d == 3 ? cv.take<double>((size_t)T * nf * L * L * 2) : nullptr;
   double* tb = d == 3 ? cv.take<double>((size_t)T * nf * nf * L * 2) : nullptr;
-  double* g64 = cv.take<double>((size_t)T * grid_cells(d, nf));
+  (void)cv.take<double>((size_t)T * grid_cells(d, nf));   // (the sizes that the workspace queries give are kept)
   float* g32 = cv.take<float>((size_t)T * grid_cells(d, nf));
   if (!cv.ok()) return FK_ENOMEM;
+  const int64_t L1 = L, nf1 = nf;
   if (d == 1) {
-    // one line per target: theta[t][q + m] -> g64[t][l] (real part)
-    hipLaunchKernelGGL(k_ifft_line, dim3(T), dim3(256), 0, ctx->stream, theta, (int64_t)1, (int64_t)L, (int64_t)0,
-                       1, m, phihat, nf, logn, g64, 1, (int64_t)1, (int64_t)nf, (int64_t)0);
+    // one line per target: theta[t][q + m] -> g32[t][l]
+    ifft_lines<true>(ctx->stream, theta, 1, L1, 0, 1, T, m, phihat, nf, logn, g32, 1, nf1, 0);
   } else if (d == 3) {
     // axis 0: for each (t, q2, q3) the line over q1 (stride L^2) -> ta[t][l1][q2][q3]
-    hipLaunchKernelGGL(k_ifft_line, dim3(T * L * L), dim3(256), 0, ctx->stream, theta, (int64_t)L * L,
-                       (int64_t)L * L * L, (int64_t)1, L * L, m, phihat, nf, logn, ta, 0, (int64_t)L * L,
-                       (int64_t)nf * L * L, (int64_t)1);
+    ifft_lines<false>(ctx->stream, theta, L1 * L1, L1 * L1 * L1, 1, L * L, T * L1 * L1, m, phihat, nf, logn, ta, L1 * L1,
+                      nf1 * L1 * L1, 1);
     // axis 1: for each (t, l1, q3) the line over q2 (stride L) -> tb[t][l1][l2][q3]
-    hipLaunchKernelGGL(k_ifft_line, dim3(T * nf * L), dim3(256), 0, ctx->stream, ta, (int64_t)L, (int64_t)L * L,
-                       (int64_t)1, L, m, phihat, nf, logn, tb, 0, (int64_t)L, (int64_t)nf * L, (int64_t)1);
-    // axis 2: for each (t, l1, l2) the contiguous line over q3 -> g64[t][l1][l2][l3] real part
-    hipLaunchKernelGGL(k_ifft_line, dim3(T * nf * nf), dim3(256), 0, ctx->stream, tb, (int64_t)1, (int64_t)L,
-                       (int64_t)0, 1, m, phihat, nf, logn, g64, 1, (int64_t)1, (int64_t)nf, (int64_t)0);
+    ifft_lines<false>(ctx->stream, ta, L1, L1 * L1, 1, L, T * nf1 * L1, m, phihat, nf, logn, tb, L1, nf1 * L1, 1);
+    // axis 2: for each (t, l1, l2) the contiguous line over q3 -> g32[t][l1][l2][l3]
+    ifft_lines<true>(ctx->stream, tb, 1, L1, 0, 1, T * nf1 * nf1, m, phihat, nf, logn, g32, 1, nf1, 0);
   } else {
-    // pass A: for each (t, q2): line over q1 (stride L) -> tmp[t][l1][q2] (complex, stride L)
-    hipLaunchKernelGGL(k_ifft_line, dim3(T * L), dim3(256), 0, ctx->stream, theta, (int64_t)L, (int64_t)L * L,
-                       (int64_t)1, L, m, phihat, nf, logn, tmp, 0, (int64_t)L, (int64_t)nf * L, (int64_t)1);
-    // pass B: for each (t, l1): line over q2 (contiguous) -> g64[t][l1][l2] real part
-    hipLaunchKernelGGL(k_ifft_line, dim3(T * nf), dim3(256), 0, ctx->stream, tmp, (int64_t)1, (int64_t)L,
-                       (int64_t)0, 1, m, phihat, nf, logn, g64, 1, (int64_t)1, (int64_t)nf, (int64_t)0);
+    // for each (t, q2): line over q1 (stride L) -> tmp[t][l1][q2]
+    ifft_lines<false>(ctx->stream, theta, L1, L1 * L1, 1, L, T * L1, m, phihat, nf, logn, tmp, L1, nf1 * L1, 1);
+    // for each (t, l1): line over q2 (contiguous) -> g32[t][l1][l2]
+    ifft_lines<true>(ctx->stream, tmp, 1, L1, 0, 1, T * nf1, m, phihat, nf, logn, g32, 1, nf1, 0);
   }
-  const int64_t gsz = (int64_t)T * (int64_t)grid_cells(d, nf);
-  hipLaunchKernelGGL(k_d2f_grid, dim3((gsz + 255) / 256), dim3(256), 0, ctx->stream, g64, g32, gsz);
   EsDev2 es{(float)(plan.beta * 1.44269504088896340736), 2.0f / (float)plan.w};
+  if (d >= 2 && plan.w <= 8) {
+    // points per wave: 64, fewer where the waves would not fill the chip
+    const int ppw = (int)std::max<int64_t>(4, std::min<int64_t>(64, nq / 4096));
+    const unsigned wb = (unsigned)((nq + 4 * ppw - 1) / (4 * ppw));
+    switch (plan.w) {
+#define FK_WAVE(WW)                                                                                                 \
+  case WW:                                                                                                          \
+    if (d == 2)                                                                                                     \
+      hipLaunchKernelGGL((k_interp_wave<WW, 2>), dim3(wb), dim3(256), 0, ctx->stream, g32, nf, T, Xq, dt, nq, ppw, es, \
+                         out, ctx->flags);                                                                          \
+    else                                                                                                            \
+      hipLaunchKernelGGL((k_interp_wave<WW, 3>), dim3(wb), dim3(256), 0, ctx->stream, g32, nf, T, Xq, dt, nq, ppw, es, \
+                         out, ctx->flags);                                                                          \
+    break;
+      FK_WAVE(4) FK_WAVE(5) FK_WAVE(6) FK_WAVE(7) FK_WAVE(8)
+#undef FK_WAVE
+      default: return FK_EINVAL;
+    }
+    FK_HIP(hipGetLastError());
+    return read_flags(ctx);
+  }
   const int blocks = (int)((nq + 255) / 256);
   FK_W_SWITCH2(plan.w, hipLaunchKernelGGL(k_interp<WW>, dim3(blocks), dim3(256), 0, ctx->stream, g32, d, nf, T, Xq,
                                           dt, nq, es, out, ctx->flags));
