@@ -349,7 +349,7 @@ def main():
         ach = nlam * N ** 3 / 3.0 / (fac_ms * 1e-3) / 1e12
         peak_s = MFMA_F16_PEAK_TFLOPS / SPLIT_TERMS
         out["roofline_solve"] = {"bound": "mfma", "kernel": "factorization (k_left_update2, k_left_update, "
-                                 "k_potrf_diag, k_trsm_panel)", "achieved": ach, "peak": peak_s,
+                                 "k_factor_diag, k_trsm_panel)", "achieved": ach, "peak": peak_s,
                                  "unit": "TFLOP/s", "frac": ach / peak_s, "factor_ms": fac_ms,
                                  "flop": nlam * N ** 3 / 3.0,
                                  "peak_basis": "f16 dense %.0f TFLOP/s / %d products per f32-accurate product"
